@@ -245,7 +245,7 @@ int afno_profile_end(double* kernel_ms, int64_t* calls);
 /*
  * Diagnostic kernel selection, process-wide.  AFNO_PATH_AUTO (the default) runs the
  * specialised kernels where the library has them and the size-generic kernels elsewhere:
- * W-axis kernels for W in {32, 180, 360}; for bf16 with H <= 96 and bs in {32, 64, 96}
+ * W-axis kernels for every even W = 2^a 3^b 5^c from 12 to 576; for bf16 with H <= 96 and bs in {32, 64, 96}
  * the column kernel that computes the H-axis DFTs as bf16 matrix-core products against a
  * DFT table (and its hidden-size variant for hidden = 2 bs); else column kernels with
  * vector-ALU FFTs for H x bs in {16 x 16, 90 x 96, 180 x 32, and for bf16 180 x 64 and

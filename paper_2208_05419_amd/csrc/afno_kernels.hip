@@ -24,6 +24,9 @@
 #include <type_traits>
 
 #include "afno_internal.h"
+#ifndef AFNO_SEPARATE_ROWS
+#include "afno_rows.hip"
+#endif
 #include "kernels_fast.h"
 #include "kernels_generic.h"
 #include "kernels_mfma.h"
@@ -35,10 +38,17 @@
 
 namespace afno {
 
+// the W-axis launchers (afno_rows.hip)
+template <typename T>
+void launch_row_fwd_fast(const Plan& pl, const T* x, T* S, PrepJob<T> pj, int64_t ntask,
+                         hipStream_t st);
+template <typename T>
+void launch_row_inv_fast(const Plan& pl, const T* S, const T* x, T* out, float* dst, int mode,
+                         hipStream_t st);
+
 // ------------------------------------------------------------------ size-specialised dispatch
 //
-// W-axis kernels: W = N1 N2, NP complex signals (2 NP channels) per workgroup.
-//   W = 32: 8 x 4, NP 32;  W = 180: 12 x 15, NP 32;  W = 360: 24 x 15, NP 16.
+// W-axis kernels: afno_rows.hip.
 // Column kernel, bf16 with H <= 96 and BS in {32, 64, 96}: H transforms as MFMA products
 //   against a transform table (kernels_mfma.h), H padded to HP in {32, 64, 96}.
 // Column kernel, vector-ALU transforms: H = N1 N2 with block size BS.
@@ -60,63 +70,9 @@ static int64_t prep_words_host(const Plan& pl, bool with_tab, int kept_h, int kp
          (with_tab ? (kp > 0 ? kept_table_tasks(hp, kp) : dft_table_tasks(hp, kept_h)) : 0);
 }
 
-// Size-specialised W-axis kernels: (W, N1, N2, NP), W = N1 N2 split into an N2-point register
-// stage and an N1-point stage after the LDS exchange, NP complex signals (2 NP channels) per
-// workgroup.  Splits and slice widths are the measured fastest per direction (W = 180: forward
-// 12 x 15 on 32 channels, inverse 15 x 12 on 64; W = 360: 15 x 24 on 32 channels both ways).
-#define AFNO_ROW_FAST_LIST(X) X(32, 8, 4, 32) X(180, 12, 15, 16) X(360, 15, 24, 16)
-#define AFNO_ROW_INV_LIST(X) X(32, 8, 4, 32) X(180, 15, 12, 32) X(360, 15, 24, 16)
-// both directions specialised for W, and C a whole number of slices in each
-bool fast_row_available(int64_t W, int64_t C) {
-  bool fwd = false, inv = false;
-#define AFNO_CASE(w, n1, n2, np) if (W == w) fwd = C % (2 * np) == 0;
-  AFNO_ROW_FAST_LIST(AFNO_CASE)
-#undef AFNO_CASE
-#define AFNO_CASE(w, n1, n2, np) if (W == w) inv = C % (2 * np) == 0;
-  AFNO_ROW_INV_LIST(AFNO_CASE)
-#undef AFNO_CASE
-  return fwd && inv;
-}
-
 bool fast_col_available(int dtype, int64_t H, int64_t bs) {
   if ((H == 16 && bs == 16) || (H == 90 && bs == 96) || (H == 180 && bs == 32)) return true;
   return dtype == 1 && H == 180 && (bs == 64 || bs == 128);
-}
-
-// pj.tout / pj.wout null: no preparation job; else its words go to extra workgroups
-template <typename T>
-static void launch_row_fwd_fast(const Plan& pl, const T* x, T* S, PrepJob<T> pj, hipStream_t st) {
-  const unsigned gx = (unsigned)(pl.B * pl.H);
-  const float sc = 0.5f * pl.row.inv_sqrt_w;
-#define AFNO_CASE(w, n1, n2, np)                                                          \
-  if (pl.W == w) {                                                                        \
-    const unsigned nmain = (unsigned)row_grid<np, (int)sizeof(T)>(gx, (int)(pl.C / (2 * np))); \
-    const unsigned nprep = pj.wout ? (unsigned)(std::min<int64_t>(                        \
-        (prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0) + np * n1 - 1) / (np * n1), 1024) \
-        + 7) / 8 * 8 : 0;                                                                 \
-    pj.nprep = (int)nprep;                                                                \
-    hipLaunchKernelGGL((row_r2c_fast<T, w, n1, n2, np>), dim3(nprep + nmain),              \
-                       dim3(np * n1), 0, st, x, S, (int)pl.C, (int)pl.KW, sc, (int64_t)gx, pj); \
-    return;                                                                               \
-  }
-  AFNO_ROW_FAST_LIST(AFNO_CASE)
-#undef AFNO_CASE
-}
-
-template <typename T>
-static void launch_row_inv_fast(const Plan& pl, const T* S, const T* x, T* out, float* dst,
-                                int mode, hipStream_t st) {
-  const unsigned gx = (unsigned)(pl.B * pl.H);
-  const float sc = pl.row.inv_sqrt_w;
-#define AFNO_CASE(w, n1, n2, np)                                                          \
-  if (pl.W == w) {                                                                        \
-    const unsigned ng = (unsigned)row_grid<np, (int)sizeof(T)>(gx, (int)(pl.C / (2 * np))); \
-    hipLaunchKernelGGL((row_c2r_fast<T, w, n1, n2, np>), dim3(ng), dim3(np * n1), 0, st,  \
-                       S, x, out, dst, (int)pl.C, (int)pl.KW, sc, mode, (int64_t)gx);     \
-    return;                                                                               \
-  }
-  AFNO_ROW_INV_LIST(AFNO_CASE)
-#undef AFNO_CASE
 }
 
 template <typename T, typename FT, int H, int N1, int N2, int BS, int WPE,
@@ -310,7 +266,8 @@ static hipError_t launch_all(const Plan& pl, const void* x, const void* w1, cons
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[1], st);
   if (row_fast)
-    launch_row_fwd_fast<T>(pl, xt, St, pj, st);
+    launch_row_fwd_fast<T>(pl, xt, St, pj,
+                           prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0), st);
   else
     hipLaunchKernelGGL(row_r2c_kernel<T>, rgrid, dim3(kRowThreads), pl.row_lds, st, xt, St, pl.row);
   e = hipGetLastError();
@@ -423,7 +380,7 @@ template <typename T>
 static hipError_t launch_row_forward(const Plan& pl, const T* x, T* S, hipStream_t st) {
   if (pl.path != 1 && fast_row_available(pl.W, pl.C)) {
     PrepJob<T> pj{nullptr, nullptr, nullptr, nullptr, (int)pl.nb, (int)pl.bs, (int)pl.H, 0, 0, -1, 0};
-    launch_row_fwd_fast<T>(pl, x, S, pj, st);
+    launch_row_fwd_fast<T>(pl, x, S, pj, 0, st);
   } else {
     dim3 rgrid((unsigned)(pl.B * pl.H), (unsigned)(pl.C / pl.row.rc));
     hipLaunchKernelGGL(row_r2c_kernel<T>, rgrid, dim3(kRowThreads), pl.row_lds, st, x, S, pl.row);

@@ -211,4 +211,12 @@ __device__ __forceinline__ uint32_t pack_c(float2 z, const bf16*) {
   return w.u;
 }
 
+// An opaque copy of a value: expressions of the copy cannot be tied to expressions of the
+// original, so each product phase of a column kernel derives its lane indices afresh rather
+// than keeping every phase's index arithmetic live across the kernel.
+__device__ __forceinline__ int opq(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 }  // namespace afno

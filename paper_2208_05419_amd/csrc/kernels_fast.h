@@ -121,49 +121,56 @@ __device__ __forceinline__ float4 split_pair(float2 z, float2 zm, float s) {
 
 // ------------------------------------------------------------------ W-axis slices
 
-// Workgroup g -> (row b H + h, first channel c0) of a W-axis kernel over nrows rows of
-// nchunk slices of 2 NP channels.  A slice narrower than a 128-byte L2 line (bf16 with
-// 2 NP = 32 channels: 64 bytes per position) shares each line with the next slice, and
-// consecutive workgroups land on different XCDs, each with its own L2; so workgroups g and
-// g + 8, which the hardware deals to the same XCD (workgroups go to the 8 XCDs in turn),
-// take the two slices of one line, and each line is fetched into one L2 only.  That grid
-// is a multiple of 16 (row_grid); workgroups past the last slice pair get no slice.
+// The W-axis kernels take the complex signals z = x_c + i x_{c+1} of all B H rows in one flat
+// order (row, channel pair), NP consecutive ones per workgroup: a slice.  C is a multiple of
+// 16, so any NP that is a multiple of 8 divides the rows into whole 16-channel pieces, and a
+// slice may run on into the next row (small C) without idle lanes; only the last slice of a
+// call can be ragged, and there the buffers' range checks drop the accesses past the end.
+//
+// A slice narrower than a 128-byte L2 line (bf16 with NP = 16: 64 bytes per position) shares
+// each line with the next slice, and consecutive workgroups land on different XCDs, each with
+// its own L2; so workgroups g and g + 8, which the hardware deals to the same XCD (workgroups
+// go to the 8 XCDs in turn), take neighbouring slices, and each line is fetched into one L2
+// only.  That grid is a multiple of 16 (row_grid); workgroups past the last slice leave.
 template <int NP, int ES>
-__host__ __device__ constexpr bool row_slices_paired(int nchunk) {
-  return 2 * NP * ES < 128 && nchunk % 2 == 0;
+__host__ __device__ constexpr bool row_slices_paired() {
+  return 2 * NP * ES < 128;
 }
 template <int NP, int ES>
-__host__ __device__ inline int64_t row_grid(int64_t nrows, int nchunk) {
-  return row_slices_paired<NP, ES>(nchunk) ? (nrows * nchunk + 15) / 16 * 16 : nrows * nchunk;
+__host__ __device__ inline int64_t row_grid(int64_t nrows, int64_t C) {
+  const int64_t slices = (nrows * (C / 2) + NP - 1) / NP;
+  return row_slices_paired<NP, ES>() ? (slices + 15) / 16 * 16 : slices;
 }
+// workgroup g -> the slice's first row and the pair it starts at in that row; false: no slice.
+// (nrows C / 16 < 2^31, checked by the host, so the arithmetic stays in 32 bits)
 template <int NP, int ES>
-__device__ __forceinline__ bool row_slice(int g, int nchunk, int64_t nrows, int64_t& row, int& c0) {
-  if (row_slices_paired<NP, ES>(nchunk)) {
-    const int pairs = nchunk / 2;
-    const int64_t unit = (int64_t)(g >> 4) * 8 + (g & 7);
-    if (unit >= nrows * pairs) return false;
-    row = unit / pairs;
-    c0 = (int)(2 * (unit % pairs) + ((g >> 3) & 1)) * (2 * NP);
-    return true;
-  }
-  row = g / nchunk;
-  c0 = (g % nchunk) * (2 * NP);
-  return true;
+__device__ __forceinline__ bool row_slice(unsigned g, int C, int64_t nrows, int64_t& row, int& pair0) {
+  static_assert(NP % 8 == 0, "whole 16-channel pieces");
+  const unsigned slice = row_slices_paired<NP, ES>() ? ((g >> 4) * 8 + (g & 7)) * 2 + ((g >> 3) & 1) : g;
+  const unsigned unit = slice * (NP / 8), per = (unsigned)C / 16;  // in pieces of eight pairs
+  const unsigned r = unit / per;
+  row = r;
+  pair0 = (int)(unit - r * per) * 8;
+  return row < nrows;
+}
+// bytes from row `row` to the end of an array of nrows rows, as a buffer size
+__device__ __forceinline__ uint32_t rows_left(int64_t nrows, int64_t row, uint64_t row_bytes) {
+  return buf_bytes((uint64_t)(nrows - row) * row_bytes);
 }
 
 // ------------------------------------------------------------------ W-axis forward
 
 // grid pj.nprep (a multiple of 8: the preparation job's workgroups, dispatched first so that
-// their longer tasks overlap the transforms) + row_grid(B H, C / (2 NP)), block NP * N1.  NP
-// complex signals (2 NP channels) per workgroup; signal p of thread t = t % NP.
+// their longer tasks overlap the transforms) + row_grid(B H, C), block NP * N1.  NP complex
+// signals per workgroup; signal p of thread t = t % NP.
 template <typename T, int W, int N1, int N2, int NP>
 __global__ void __launch_bounds__(NP * N1)
 row_r2c_fast(const T* __restrict__ x, T* __restrict__ S, int C, int KW, float scale,
              int64_t nrows, PrepJob<T> pj) {
   static_assert(N1 * N2 == W && W % 2 == 0, "W = N1 N2, even");
-  static_assert(N2 * N1 * NP >= 96, "room for the table's roots");
   constexpr int NT = NP * N1;
-  __shared__ float2 F[N2 * N1 * NP];
+  constexpr int FN = N2 * N1 * NP > 96 ? N2 * N1 * NP : 96;  // room for the table's roots
+  __shared__ float2 F[FN];
   __shared__ float2 tw[W];
   if ((int)blockIdx.x < pj.nprep) {  // the column kernel's operands
     if (pj.tout && pj.kept_h >= 0) dft_roots(F, pj.H);
@@ -171,19 +178,26 @@ row_r2c_fast(const T* __restrict__ x, T* __restrict__ S, int C, int KW, float sc
     return;
   }
   const int tid = threadIdx.x;
-  // the workgroup's row b H + h and channel slice (pj.nprep is a multiple of 8, so workgroup
-  // g keeps its XCD: consecutive workgroups go to consecutive XCDs)
+  // the workgroup's slice (pj.nprep is a multiple of 8, so workgroup g keeps its XCD:
+  // consecutive workgroups go to consecutive XCDs)
   int64_t row;
-  int c0;
-  if (!row_slice<NP, (int)sizeof(T)>(blockIdx.x - pj.nprep, C / (2 * NP), nrows, row, c0)) return;
+  int pair0;
+  if (!row_slice<NP, (int)sizeof(T)>(blockIdx.x - pj.nprep, C, nrows, row, pair0)) return;
   constexpr uint32_t es = sizeof(T);
   const uint32_t xrow = (uint32_t)C * es;        // bytes between consecutive w
   const uint32_t srow = (uint32_t)C * 2 * es;    // bytes between consecutive kw of S
-  const Buf xb(x + row * (int64_t)W * C + c0, (uint32_t)W * xrow);
-  const Buf sb(S + (row * (int64_t)KW * C + c0) * 2, (uint32_t)KW * srow);
+  const Buf xb(x + row * (int64_t)W * C, rows_left(nrows, row, (uint64_t)W * xrow));
+  const Buf sb(S + row * (int64_t)KW * C * 2, rows_left(nrows, row, (uint64_t)KW * srow));
+  const int p = tid % NP, j = tid / NP;
+  // this thread's signal: pair cp of row `row` + dr (NT is a multiple of NP: also that of its
+  // second-stage tasks)
+  uint32_t dr = 0, cp = pair0 + p;
+  if (pair0 + NP > C / 2) {  // the slice runs on into the next row (uniform)
+    dr = cp / (uint32_t)(C / 2);
+    cp -= dr * (uint32_t)(C / 2);
+  }
   {
-    const int p = tid % NP, j = tid / NP;
-    const uint32_t voff = 2 * p * es + j * xrow;
+    const uint32_t voff = 2 * cp * es + dr * (W * xrow) + j * xrow;
     float2 v[N2];
 #pragma unroll
     for (int t = 0; t < N2; ++t) v[t] = ld_pair(xb, (const T*)nullptr, voff, N1 * t * xrow);
@@ -195,39 +209,39 @@ row_r2c_fast(const T* __restrict__ x, T* __restrict__ S, int C, int KW, float sc
       F[(k2 * N1 + j) * NP + p] = k2 == 0 ? v[0] : twiddle<false>(v[k2], tw, j * k2);
   }
   __syncthreads();
-  // One task per pair of residues {q, N2 - q}: it holds Z[k] and its partner Z[W - k]
-  // for every k of both residue classes, so the two real spectra separate in registers.
-  constexpr int NPT = N2 / 2 + 1;
-  for (int task = tid; task < NP * NPT; task += NT) {
-    const int p = task % NP, q = task / NP;
-    const int qa = q, qb = (N2 - q) % N2;
+  // One task per pair of residues {q, N2 - q}: it holds Z[k] and its partner Z[W - k] for every
+  // k of both residue classes, so the two real spectra separate in registers.  Residues 0 and
+  // (N2 even) N2 / 2 are their own partners and share task 0.
+  constexpr int NPT = (N2 + 1) / 2;
+  const uint32_t vs = 4 * cp * es + dr * (KW * srow);
+  for (int q = j; q < NPT; q += N1) {
+    const int qa = q, qb = q == 0 ? (N2 % 2 == 0 ? N2 / 2 : 0) : N2 - q;
     float2 a[N1], b[N1];
 #pragma unroll
-    for (int j = 0; j < N1; ++j) {
-      a[j] = F[(qa * N1 + j) * NP + p];
-      b[j] = F[(qb * N1 + j) * NP + p];
+    for (int i = 0; i < N1; ++i) {
+      a[i] = F[(qa * N1 + i) * NP + p];
+      b[i] = F[(qb * N1 + i) * NP + p];
     }
     DftReg<N1, false>::run(a);  // a[k1] = Z[qa + N2 k1]
     DftReg<N1, false>::run(b);  // b[k1] = Z[qb + N2 k1]
-    const uint32_t va = 4 * p * es + qa * srow, vb = 4 * p * es + qb * srow;
+    const uint32_t va = vs + qa * srow, vb = vs + qb * srow;
 #pragma unroll
     for (int k1 = 0; k1 < N1; ++k1) {
-      // partner of qa + N2 k1: N2 (N1 - k1) for q = 0, else qb + N2 (N1 - 1 - k1)
-      const int ka = qa + N2 * k1;
-      const float2 zam = (q == 0) ? a[(N1 - k1) % N1] : b[N1 - 1 - k1];
+      // partner of q + N2 k1: N2 (N1 - k1) for q = 0, else (N2 - q) + N2 (N1 - 1 - k1)
+      const int ka = qa + N2 * k1, kb = qb + N2 * k1;
+      const float2 zam = q == 0 ? a[(N1 - k1) % N1] : b[N1 - 1 - k1];
+      const float2 zbm = q == 0 ? b[N1 - 1 - k1] : a[N1 - 1 - k1];
       if (ka <= W / 2 && ka < KW)
         st_cpair(sb, (const T*)nullptr, va, N2 * k1 * srow, split_pair(a[k1], zam, scale));
-      const int kb = qb + N2 * k1;
       if (qb != qa && kb <= W / 2 && kb < KW)
-        st_cpair(sb, (const T*)nullptr, vb, N2 * k1 * srow, split_pair(b[k1], a[N1 - 1 - k1], scale));
+        st_cpair(sb, (const T*)nullptr, vb, N2 * k1 * srow, split_pair(b[k1], zbm, scale));
     }
   }
 }
 
 // ------------------------------------------------------------------ W-axis inverse + residual
 
-// grid row_grid(B H, C / (2 NP)), block NP * N1.  mode 0: out = x + y (dtype T); mode 1:
-// dst = y.
+// grid row_grid(B H, C), block NP * N1.  mode 0: out = x + y (dtype T); mode 1: dst = y.
 // Global traffic goes through LDS in 16-byte vectors: the kept half spectrum of the
 // workgroup's 2 NP channels is staged once (each stored bin feeds both Z[k] and Z[W-k]),
 // the residual is prefetched at kernel start, and the output leaves in 16-byte stores.
@@ -249,26 +263,37 @@ row_c2r_fast(const T* __restrict__ S, const T* __restrict__ x, T* __restrict__ o
   __shared__ float2 tw[W];
   const int tid = threadIdx.x;
   int64_t row;
-  int c0;
-  if (!row_slice<NP, (int)sizeof(T)>(blockIdx.x, C / (2 * NP), nrows, row, c0)) return;
+  int pair0;
+  if (!row_slice<NP, (int)sizeof(T)>(blockIdx.x, C, nrows, row, pair0)) return;
   const uint32_t xrow = (uint32_t)C * es;
   const uint32_t srow = (uint32_t)C * 2 * es;
-  const int64_t xbase = row * (int64_t)W * C + c0;
-  const Buf xb(x + xbase, (uint32_t)W * xrow);
-  const Buf ob(out + xbase, (uint32_t)W * xrow);
-  const Buf db(dst + xbase, (uint32_t)W * C * 4);
-  const Buf sb(S + (row * (int64_t)KW * C + c0) * 2, (uint32_t)KW * srow);
+  const int64_t xbase = row * (int64_t)W * C;
+  const Buf xb(x + xbase, rows_left(nrows, row, (uint64_t)W * xrow));
+  const Buf ob(out + xbase, rows_left(nrows, row, (uint64_t)W * xrow));
+  const Buf db(dst + xbase, rows_left(nrows, row, (uint64_t)W * C * 4));
+  const Buf sb(S + row * (int64_t)KW * C * 2, rows_left(nrows, row, (uint64_t)KW * srow));
+  // NT is a multiple of XPR and of SPR, so a thread moves one 16-byte vector position of the
+  // slice (channels 2 pair0 + XV g of x and out, bins of channels 2 pair0 + (XV / 2) v of S) at
+  // every w and kw it handles: its byte offset within row w or kw = 0, found once
+  static_assert(NT % XPR == 0 && NT % SPR == 0, "one vector position per thread");
+  const bool one_row = pair0 + NP <= C / 2;  // else the slice runs on into the next row
+  auto slice_off = [&](int c, uint32_t cbytes, uint32_t row_bytes) {
+    const uint32_t f = 2 * pair0 + c, r = one_row ? 0 : f / (uint32_t)C;
+    return r * row_bytes + (f - r * (uint32_t)C) * cbytes;
+  };
+  auto x_off = [&](int t) { return slice_off((t % XPR) * XV, es, W * xrow); };
   uint4* F4 = reinterpret_cast<uint4*>(F);
   // ---- the kept half spectrum of the slice and the residual, 16-byte loads
   {
+    const uint32_t soff = slice_off((tid % SPR) * (XV / 2), 2 * es, KW * srow);
     uint4 sv[((HALF + 1) * SPR + NT - 1) / NT];
 #pragma unroll
     for (int u = 0; u < ((HALF + 1) * SPR + NT - 1) / NT; ++u) {
       const int i = tid + u * NT;
-      const int r = i / SPR, v = i % SPR;
+      const int r = i / SPR;
       sv[u] = make_uint4(0, 0, 0, 0);
       if (r < KW && r <= HALF) {
-        const auto q = __builtin_amdgcn_raw_buffer_load_b128(sb.r, v * 16 + r * srow, 0, 0);
+        const auto q = __builtin_amdgcn_raw_buffer_load_b128(sb.r, soff + r * srow, 0, 0);
         sv[u] = make_uint4(q[0], q[1], q[2], q[3]);
       }
     }
@@ -281,10 +306,11 @@ row_c2r_fast(const T* __restrict__ S, const T* __restrict__ x, T* __restrict__ o
   }
   uint4 xres[TX];
   if (mode == 0) {
+    const uint32_t xoff = x_off(tid);
 #pragma unroll
     for (int u = 0; u < TX; ++u) {
-      const int i = min(tid + u * NT, W * XPR - 1);
-      const auto q = __builtin_amdgcn_raw_buffer_load_b128(xb.r, (i % XPR) * 16 + (i / XPR) * xrow, 0, 0);
+      const int w = min(tid / XPR + u * (NT / XPR), W - 1);
+      const auto q = __builtin_amdgcn_raw_buffer_load_b128(xb.r, xoff + w * xrow, 0, 0);
       xres[u] = make_uint4(q[0], q[1], q[2], q[3]);
     }
   }
@@ -341,6 +367,7 @@ row_c2r_fast(const T* __restrict__ S, const T* __restrict__ x, T* __restrict__ o
   __syncthreads();
   // ---- out = x + y / sqrt(W) (or dst = y), 16-byte vectors along each row
   if (mode == 0) {
+    const uint32_t xoff = x_off(opq(tid));  // derived afresh, not kept through the transforms
 #pragma unroll
     for (int u = 0; u < TX; ++u) {
       const int i = tid + u * NT;
@@ -361,17 +388,18 @@ row_c2r_fast(const T* __restrict__ S, const T* __restrict__ x, T* __restrict__ o
           for (int e = 0; e < 4; ++e)
             ov.w32[e] = __float_as_uint(__uint_as_float(xo.w32[e]) + yr[e] * scale);
         }
-        ob.st128(ov.u4, g * 16 + w * xrow, 0);
+        ob.st128(ov.u4, xoff + w * xrow, 0);
       }
     }
   } else {
     constexpr int DPR = 2 * NP / 4;  // 16-byte float vectors per row of dst
     for (int i = tid; i < W * DPR; i += NT) {
       const int w = i / DPR, g = i % DPR;
+      const uint32_t doff = slice_off(4 * g, 4, (uint32_t)(W * C) * 4);
       const float4 y = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(F + w * NP) + 4 * g);
       db.st128(make_uint4(__float_as_uint(y.x * scale), __float_as_uint(y.y * scale),
                           __float_as_uint(y.z * scale), __float_as_uint(y.w * scale)),
-               g * 16 + w * (uint32_t)C * 4, 0);
+               doff + w * (uint32_t)C * 4, 0);
     }
   }
 }

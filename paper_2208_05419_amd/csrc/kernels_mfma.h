@@ -34,15 +34,6 @@
 
 namespace afno {
 
-// An opaque copy of a value: expressions of the copy cannot be tied to expressions of the
-// original, so each product phase of a column kernel derives its lane indices afresh rather
-// than keeping every phase's index arithmetic live across the kernel.
-__device__ __forceinline__ int opq(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
-
 // Geometry for padded height HP (H <= HP, HP a multiple of 32) and block size BS; NWR x NWC
 // waves (transposed products: NWR along the channel entries, NWC along the rows; layer 2 the
 // other way round).

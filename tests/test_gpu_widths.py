@@ -1,0 +1,45 @@
+"""Every width of the size-specialised W-axis passes against the float64 oracle, at channel
+counts whose 16- and 32-signal slices run on into the next row and end ragged (C = 16: eight
+signals a row; C = 48 and 80: slices that straddle rows), an odd number of rows, with and
+without a cutoff, in both storage types and both directions' splits.
+
+Bars as the other parity tests: the filter's delta (float32 stage output, which takes the
+inverse pass's float store) and out within 1e-4 (fp32) or 2e-2 (bf16) of max |r|."""
+import numpy as np
+import pytest
+
+import paper_2208_05419_amd as afno
+from paper_2208_05419_amd import synth
+from gpu_util import TOL, dev_weights, max_rel, oracle_run, say, to_dev, to_f64
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+WIDTHS = [n for n in range(12, 577, 2)
+          if any(n == 2 ** a * 3 ** b * 5 ** c for a in range(1, 11) for b in range(6) for c in range(5))]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    afno.load_library()
+
+
+@pytest.mark.parametrize("W", WIDTHS)
+def test_width(W):
+    i = WIDTHS.index(W)
+    C, H, keep = (16, 48, 80)[i % 3], (1, 3, 5)[(i // 3) % 3], (1.0, 0.6)[i % 2]
+    for dtype in ("fp32", "bf16"):
+        wl = synth.Workload("width", 1 + i % 2, H, W, C, C // 16, dtype, 0.01, keep, weight_std=0.2)
+        say(f"[width] B={wl.B} H={H} W={W} C={C} {dtype} keep={keep}")
+        x_st, w_st = synth.make_x(wl, seed=W), synth.make_weights(wl, seed=W)
+        x, w = to_dev(x_st, dtype), dev_weights(w_st, dtype)
+        args = (x, w["w1"], w["b1"], w["w2"], w["b2"], wl.num_blocks, wl.lam, keep)
+        out = afno.filter_forward(*args)
+        delta = afno.filter_stage(*args, afno.AFNO_STAGE_DELTA)
+        torch.cuda.synchronize()
+        ref, st = oracle_run(x_st, w_st, wl, stages=True)
+        e_out, e_delta = max_rel(to_f64(out), ref), max_rel(to_f64(delta), st["delta"])
+        say(f"  out rel {e_out:.2e}  delta rel {e_delta:.2e}")
+        assert np.isfinite(e_out) and e_out <= TOL[dtype] and e_delta <= TOL[dtype]
