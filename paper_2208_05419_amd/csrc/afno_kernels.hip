@@ -349,11 +349,14 @@ int wgrad_slab_chunks(const Plan& pl, int* kchunk) {
   return (int)((mpad + kc - 1) / kc);
 }
 
-// mode chunks of the size-generic weight-product kernel: whole 32-mode steps, at most 32
+// mode chunks of the size-generic weight-product kernel: whole 32-mode steps, about 4,096
+// waves (16 per compute unit) with its tiles, a chunk no shorter than 128 modes (four steps)
+// and at most 128 of them (wgrad_finalize_parts reads each chunk's whole product)
 static int wgrad_generic_chunks(const Plan& pl, int* kchunk) {
   const int64_t mpad = bwd_mpad(pl);
-  const int64_t nk = std::max<int64_t>(1, std::min<int64_t>(32, (mpad + 4095) / 4096));
-  const int64_t kc = ((mpad + nk - 1) / nk + 31) / 32 * 32;
+  const int64_t tiles = 2 * pl.nb * (pl.bs / 16) * (pl.bs / 16);
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>({128, 4096 / tiles, mpad / 128}));
+  const int64_t kc = ((mpad + want - 1) / want + 31) / 32 * 32;
   *kchunk = (int)kc;
   return (int)((mpad + kc - 1) / kc);
 }
@@ -493,13 +496,13 @@ static hipError_t launch_bwd(const Plan& pl, const BwdPtrs& a, hipStream_t st) {
       hipLaunchKernelGGL(wgrad_slab<192>, sgrid, dim3(1024), 512 * 192, st,
                          reinterpret_cast<const bf16*>(modes), mpad, nb, kchunk, acc, bsums);
   } else {
-    // 64 x 64 output tiles, chunks of whole 32-mode steps
-    const int nt64 = (nb2 + 63) / 64;
-    const dim3 wgrid((unsigned)(2 * nb * nt64 * nt64), (unsigned)nchunk);
+    // 32 x 32 output tiles, four to a workgroup
+    const int nt = bs / 16;
+    const dim3 wgrid((unsigned)((2 * nb * nt * nt + 3) / 4), (unsigned)nchunk);
     hipLaunchKernelGGL(wgrad_kernel<T>, wgrid, dim3(256), 0, st, modes, mpad, nb, bs, kchunk, acc,
                        bsums);
   }
-  hipLaunchKernelGGL(wgrad_finalize_parts, dim3((unsigned)std::min<int64_t>((nw + 255) / 256, 4096)),
+  hipLaunchKernelGGL(wgrad_finalize_parts, dim3((unsigned)(nw / 64)),
                      dim3(256), 0, st, acc, nchunk, bsums, nb, bs, a.dw1, a.dw2, a.db1, a.db2);
   return hipGetLastError();
 }

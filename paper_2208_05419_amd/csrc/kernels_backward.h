@@ -327,98 +327,126 @@ column_bwd_kernel(const T* __restrict__ Sx, T* __restrict__ Sg, const T* __restr
 // (dW2) A = h, B = do; part[chunk][layer][blk][r][s] = sum over the chunk's modes of
 // A[r][m] B[s][m] (r, s the 2 bs real entries, (c, rho) interleaved), and
 // bpart[chunk][layer][blk][s] = sum of B[s][m] (the bias gradients db1, db2): plain stores,
-// one workgroup per output value and chunk, summed over the chunks by wgrad_finalize_parts in
+// one wave per output value and chunk, summed over the chunks by wgrad_finalize_parts in
 // chunk order, so repeated calls give the same bits.
-// grid (2 nb tiles64^2, nchunk = ceil(mpad / kchunk)), 256 threads: four waves with 32 x 32
-// each of a 64 x 64 output tile; kchunk a multiple of 32.
+//
+// A wave owns a 32 x 32 output tile (2 bs is a multiple of 32: no ragged tile) over one chunk
+// of kchunk modes (a multiple of 32), 32 modes a step, the next step's words in flight during
+// the current products; there is no barrier, so waves only wait for their own loads.  Every
+// load is 16 bytes per lane.  In fp32 lane group g loads modes 4 g .. 4 g + 3 of 16 and feeds
+// value j of the four to the j-th matrix instruction: the product sums over the modes, so any
+// order serves as long as both operands take the same one.  What bounds it is the operands'
+// trip through the caches (each is read by 2 bs / 32 waves) and, with few chunks, latency:
+// 72 x 144 x 384 fp32 (8 blocks of 48, 7,008 modes): 400 us as 128 workgroups of 64 x 64 tiles
+// with 4-byte loads and 2 chunks, 32 us as 4,032 waves in 28 chunks.
+// grid (ceil(2 nb (2 bs / 32)^2 / 4), nchunk = ceil(mpad / kchunk)), 256 threads.
 template <typename T>
 __global__ void __launch_bounds__(256) wgrad_kernel(const T* __restrict__ modes, int64_t mpad,
                                                     int nb, int bs, int kchunk,
                                                     float* __restrict__ part,
                                                     float* __restrict__ bpart) {
   typedef Mma<T> M;
-  const int nb2 = 2 * bs;
-  const int nt64 = (nb2 + 63) / 64;
-  int g = blockIdx.x;
-  const int ts = g % nt64; g /= nt64;
-  const int tr = g % nt64; g /= nt64;
-  const int blk = g % nb; g /= nb;
-  const int layer = g;  // 0: dW1, 1: dW2
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r0 = 64 * tr + 32 * (wave >> 1), s0 = 64 * ts + 32 * (wave & 1);
-  const T* A = modes + ((int64_t)(layer ? kModeH : kModeX) * nb + blk) * nb2 * mpad;
-  const T* Bm = modes + ((int64_t)(layer ? kModeDo : kModeDv) * nb + blk) * nb2 * mpad;
+  constexpr int LD = sizeof(T) == 2 ? 1 : 2;  // 16-byte loads per 16 entries and 32 modes
+  const int nb2 = 2 * bs, nt = nb2 / 32;
+  int g = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (g >= 2 * nb * nt * nt) return;
+  const int ts = g % nt; g /= nt;
+  const int tr = g % nt; g /= nt;
+  const int blk = g % nb;
+  const int layer = g / nb;  // 0: dW1, 1: dW2
+  const int lane = threadIdx.x & 63, l16 = lane & 15, gq = lane >> 4;
+  const int r0 = 32 * tr, s0 = 32 * ts;
   const int64_t k0 = (int64_t)blockIdx.y * kchunk;
   const int64_t k1 = k0 + kchunk < mpad ? k0 + kchunk : mpad;
+  // this lane's word of step 0: bf16 the eight modes of group gq; fp32 half gq % 2 of group
+  // gq / 2 (its second load: two groups on)
+  const int64_t grp = (k0 >> 3) + (sizeof(T) == 2 ? gq : gq >> 1);
+  const int half = sizeof(T) == 2 ? 0 : 4 * (gq & 1);
+  const T* A = modes + (((int64_t)(layer ? kModeH : kModeX) * nb + blk) * mpad / 8 + grp) * nb2 * 8 +
+               (r0 + l16) * 8 + half;
+  const T* Bm = modes + (((int64_t)(layer ? kModeDo : kModeDv) * nb + blk) * mpad / 8 + grp) * nb2 * 8 +
+                (s0 + l16) * 8 + half;
+  const int64_t step = (int64_t)4 * nb2 * 8;  // 32 modes
+  const int sub = 2 * nb2 * 8;                // fp32: the second 16 modes
   f32x4 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bool rv[2] = {r0 < nb2, r0 + 16 < nb2}, sv[2] = {s0 < nb2, s0 + 16 < nb2};
-  const int l16 = lane & 15, gq = lane >> 4;
-  // the two waves of the first row tile also sum their B fragments: entries s0 + 16 j + l16,
-  // this lane's modes of each k-step
-  const bool bias_wave = tr == 0 && (wave >> 1) == 0;
   float bsum[2] = {0.f, 0.f};
-  for (int64_t k = k0; k < k1; k += M::kK) {
-    typename M::Frag a[2], bfr[2];
+  V16 a[2][LD], b[2][LD];
+  auto load = [&](V16 (&pa)[2][LD], V16 (&pb)[2][LD]) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r = rv[i] ? r0 + 16 * i + l16 : 0;
-      const int s = sv[i] ? s0 + 16 * i + l16 : 0;
-      if constexpr (sizeof(T) == 2) {  // eight modes k + 8 gq .. + 7: one group
-        const int64_t grp = (k >> 3) + gq;
-        a[i] = *reinterpret_cast<const bf16x8*>(A + (grp * nb2 + r) * 8);
-        bfr[i] = *reinterpret_cast<const bf16x8*>(Bm + (grp * nb2 + s) * 8);
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < LD; ++q) {
+        pa[i][q].u = *reinterpret_cast<const uint4*>(A + 16 * 8 * i + q * sub);
+        pb[i][q].u = *reinterpret_cast<const uint4*>(Bm + 16 * 8 * i + q * sub);
+      }
+    A += step;
+    Bm += step;
+  };
+  load(a, b);
+  for (int64_t k = k0; k < k1; k += 32) {
+    V16 an[2][LD], bn[2][LD];
+    if (k + 32 < k1) load(an, bn);
+#pragma unroll
+    for (int q = 0; q < LD; ++q) {
+      if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = mma_bf16(a[i][q].u, b[j][q].u, acc[i][j]);
       } else {
-        const int64_t md = k + gq;
-        a[i] = A[((md >> 3) * nb2 + r) * 8 + (md & 7)];
-        bfr[i] = Bm[((md >> 3) * nb2 + s) * 8 + (md & 7)];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = M::mma(a[i][q].f[e], b[j][q].f[e], acc[i][j]);
+      }
+      if (tr == 0) {  // the waves of the first row tile also sum their B words
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          float s = 0.f;
+          if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += (float)b[j][q].h[e];
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s += b[j][q].f[e];
+          }
+          bsum[j] += s;
+        }
       }
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = M::mma(a[i], bfr[j], acc[i][j]);
-    if (bias_wave) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if constexpr (sizeof(T) == 2) {
-          float s8 = 0.f;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) s8 += (float)bfr[j][q];
-          bsum[j] += s8;
-        } else {
-          bsum[j] += bfr[j];
-        }
+      for (int q = 0; q < LD; ++q) {
+        a[i][q] = an[i][q];
+        b[i][q] = bn[i][q];
       }
-    }
   }
   const int64_t slot = ((int64_t)blockIdx.y * 2 + layer) * nb + blk;
-  if (bias_wave) {
+  if (tr == 0) {
     // the four lane groups hold different modes of the same entry: a fixed butterfly
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       float v = bsum[j];
       v += __shfl_xor(v, 16);
       v += __shfl_xor(v, 32);
-      if (gq == 0 && sv[j]) bpart[slot * nb2 + s0 + 16 * j + l16] = v;
+      if (gq == 0) bpart[slot * nb2 + s0 + 16 * j + l16] = v;
     }
   }
   float* out = part + slot * nb2 * nb2;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (!rv[i] || !sv[j]) continue;
-      const int s = s0 + 16 * j + l16;
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = r0 + 16 * i + 4 * gq + q;
-        out[(int64_t)r * nb2 + s] = acc[i][j][q];
-      }
-    }
+      for (int q = 0; q < 4; ++q)
+        out[(int64_t)(r0 + 16 * i + 4 * gq + q) * nb2 + s0 + 16 * j + l16] = acc[i][j][q];
 }
 
 // bf16 weight-gradient products for 2 bs = NB2 a multiple of 64: one workgroup per (layer,
@@ -573,40 +601,54 @@ __global__ void __launch_bounds__(1024) wgrad_slab(const bf16* __restrict__ mode
 // dW (re, im) from the weight-product kernels' chunk sums part[chunk][2][nb][2 bs][2 bs]: for
 // entries r = (i, rho), s = (j, sigma), dW[i][j] = (P[(i,0)][(j,0)] + P[(i,1)][(j,1)],
 // P[(i,0)][(j,1)] - P[(i,1)][(j,0)]) (conj(a) b summed); db1, db2 from the chunk bias sums
-// bpart[chunk][2][nb][2 bs]; each summed over the chunks here in chunk order.  Grid over
-// 2 nb bs^2.
+// bpart[chunk][2][nb][2 bs].  A call has few outputs (37 thousand for 8 blocks of 48) and up to
+// 128 chunks, so it is bound by the loads in flight: wave w of a workgroup's four adds up chunks
+// w, w + 4, ... of the workgroup's 64 outputs, in that order, and the four sums are added in
+// order (28 chunks of 8 blocks of 48: 11.8 us with one thread per output, 6.2 us).  Grid
+// 2 nb bs^2 / 64 (bs is a multiple of 16), 256 threads.
 __global__ void __launch_bounds__(256) wgrad_finalize_parts(const float* __restrict__ part,
                                                             int nchunk, const float* __restrict__ bpart,
                                                             int nb, int bs, float* __restrict__ dw1,
                                                             float* __restrict__ dw2,
                                                             float* __restrict__ db1,
                                                             float* __restrict__ db2) {
+  __shared__ float sre[4][64], sim[4][64], sbias[4][64];
   const int nb2 = 2 * bs;
   const int64_t n = (int64_t)nb * bs * bs;
   const int64_t nbias = (int64_t)nb * nb2;
   const int64_t cstride = (int64_t)2 * nb * nb2 * nb2;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < 2 * n;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int layer = t >= n ? 1 : 0;
-    const int64_t u = t - layer * n;
-    const int64_t k = u / ((int64_t)bs * bs);
-    const int r = (int)(u - k * bs * bs), i = r / bs, j = r % bs;
-    const float* P = part + ((int64_t)layer * nb + k) * nb2 * nb2;
-    float rr = 0.f, ii = 0.f, ri = 0.f, ir = 0.f;
-    for (int c = 0; c < nchunk; ++c, P += cstride) {
-      rr += P[(2 * i) * nb2 + 2 * j];
-      ii += P[(2 * i + 1) * nb2 + 2 * j + 1];
-      ri += P[(2 * i) * nb2 + 2 * j + 1];
-      ir += P[(2 * i + 1) * nb2 + 2 * j];
-    }
-    float* d = (layer ? dw2 : dw1) + ((k * bs + i) * bs + j) * 2;
-    d[0] = rr + ii;
-    d[1] = ri - ir;
-    if (t < 2 * nbias) {
-      float sb = 0.f;
-      for (int c = 0; c < nchunk; ++c) sb += bpart[(int64_t)c * 2 * nbias + t];
-      (t < nbias ? db1 : db2)[t < nbias ? t : t - nbias] = sb;
-    }
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t t = (int64_t)blockIdx.x * 64 + l;  // < 2 n
+  const int layer = t >= n ? 1 : 0;
+  const int64_t u = t - layer * n;
+  const int64_t k = u / ((int64_t)bs * bs);
+  const int r = (int)(u - k * bs * bs), i = r / bs, j = r % bs;
+  const float* P = part + ((int64_t)layer * nb + k) * nb2 * nb2 + (2 * i) * nb2 + 2 * j + w * cstride;
+  float rr = 0.f, ii = 0.f, ri = 0.f, ir = 0.f;
+#pragma unroll 4
+  for (int c = w; c < nchunk; c += 4, P += 4 * cstride) {
+    const float2 p0 = *reinterpret_cast<const float2*>(P);
+    const float2 p1 = *reinterpret_cast<const float2*>(P + nb2);
+    rr += p0.x;
+    ri += p0.y;
+    ir += p1.x;
+    ii += p1.y;
+  }
+  sre[w][l] = rr + ii;
+  sim[w][l] = ri - ir;
+  if (t < 2 * nbias) {
+    float sb = 0.f;
+    for (int c = w; c < nchunk; c += 4) sb += bpart[(int64_t)c * 2 * nbias + t];
+    sbias[w][l] = sb;
+  }
+  __syncthreads();
+  if (w != 0) return;
+  float* d = (layer ? dw2 : dw1) + ((k * bs + i) * bs + j) * 2;
+  d[0] = ((sre[0][l] + sre[1][l]) + sre[2][l]) + sre[3][l];
+  d[1] = ((sim[0][l] + sim[1][l]) + sim[2][l]) + sim[3][l];
+  if (t < 2 * nbias) {
+    const float sb = ((sbias[0][l] + sbias[1][l]) + sbias[2][l]) + sbias[3][l];
+    (t < nbias ? db1 : db2)[t < nbias ? t : t - nbias] = sb;
   }
 }
 
