@@ -96,7 +96,8 @@ int afno_filter_forward(const void* x, const void* w1, const void* b1, const voi
  * (fp32), then the prepared block weights and the DFT table, about 1.2 MB for 8 blocks of 96)
  * is an array of AFNO_NOALLOC_MAX_WORKSPACE bytes in device memory that the library holds on
  * every GPU it runs on until the process ends (the 90 x 180 x 768 bf16 filter fits up to
- * B = 5).  AFNO_ERR_UNSUPPORTED, before any HIP call, when the workspace would be larger.
+ * B = 5).  AFNO_ERR_UNSUPPORTED, before any HIP call, when the workspace would be larger; the
+ * size-generic column kernels do without the prepared weights where only those would not fit.
  * Every call on a GPU uses that GPU's one array, which keeps the last call's contents (each
  * call writes all it reads): calls whose work overlaps in time on one GPU (different streams
  * or host threads without ordering between them) race and leave out undefined; calls on one
@@ -210,9 +211,9 @@ int afno_filter_stage_hidden(const void* x, const void* w1, const void* b1, cons
  *   dw1, dw2 [nb][bs][bs][2]  float32, device memory, overwritten (not accumulated)
  *   db1, db2 [nb][bs][2]      float32, device memory, overwritten
  * No output may overlap an input or another output (AFNO_ERR_ALIAS).  The library
- * allocates stream-ordered workspace on `stream`: two spectra, the conjugate-transposed
+ * allocates stream-ordered workspace on `stream`: two spectra, the prepared
  * weights, four per-mode factor tensors of nb * 2 bs * B * kept_w * ceil32(ceil16(H)) values
- * in dtype, and float32 chunk sums (2 nb 2 bs (2 bs + 1) per chunk of modes, at most 64
+ * in dtype, and float32 chunk sums (2 nb 2 bs (2 bs + 1) per chunk of modes, at most 128
  * chunks).  B == 0 or nothing kept: dx = gout and zero weight and bias gradients.  Errors as
  * afno_filter_forward; AFNO_ERR_UNSUPPORTED also when a column of the backward kernel (one
  * tile of H x bs complex values plus two bit masks) does not fit the LDS.  Reproducibility:

@@ -65,6 +65,13 @@ struct Args {
   int64_t hs;        // hidden units per block; 0: the block size
 };
 
+// LDS a column may take: its tiles, 32 (16) channels in float and the roots.  Every column
+// kernel needs at most this much, so it is the limit the entry points state.
+size_t column_lds_limit(const afno::ColParams& c) {
+  return (size_t)c.tile_bytes + (size_t)c.htile_bytes +
+         (size_t)c.H * (c.bs % 32 == 0 ? 32 : 16) * 8 + (size_t)c.H * 8;
+}
+
 // Validation (no HIP call) and plan construction.  Returns AFNO_OK, or an error code
 // with g_last_error set.
 int make_plan(const Args& a, afno::Plan& pl) {
@@ -101,7 +108,8 @@ int make_plan(const Args& a, afno::Plan& pl) {
   if (!aligned(a.w1, 4) || !aligned(a.b1, 4) || !aligned(a.w2, 4) || !aligned(a.b2, 4))
     return fail(AFNO_ERR_UNSUPPORTED, "weights and biases must be 4-byte aligned");
   if (a.W % 2 != 0) return fail(AFNO_ERR_UNSUPPORTED, "W must be even");
-  if (!factorize(a.W, pl.row.rw) || !factorize(a.H, pl.col.rh))
+  afno::Radices rh;
+  if (!factorize(a.W, pl.row.rw) || !factorize(a.H, rh))
     return fail(AFNO_ERR_UNSUPPORTED, "H and W must be of the form 2^a 3^b 5^c");
   if (pl.bs % 16 != 0 || pl.bs > 128)
     return fail(AFNO_ERR_UNSUPPORTED, "block size C/num_blocks must be a multiple of 16 and <= 128");
@@ -150,26 +158,20 @@ int make_plan(const Args& a, afno::Plan& pl) {
   c.hs = (int)hs;
   c.ldt = 2 * c.bs + (a.dtype == AFNO_DTYPE_BF16 ? 8 : 4);
   c.ldh = 2 * c.hs + (a.dtype == AFNO_DTYPE_BF16 ? 8 : 4);
-  c.chk = (c.bs % 32 == 0) ? 32 : 16;  // must divide bs
-  {  // waves: one per 32 real output columns of the wider layer, 4 to 8
-    const int64_t wmax = std::max<int64_t>(c.bs, c.hs) / 16;
-    pl.col_threads = 64 * (int)std::min<int64_t>(8, std::max<int64_t>(4, wmax));
-  }
   c.tile_bytes = (int)(((size_t)c.H16 * c.ldt * es + 15) / 16 * 16);
   c.htile_bytes = c.hs == c.bs ? 0 : (int)(((size_t)c.H16 * c.ldh * es + 15) / 16 * 16);
-  pl.col_lds = (size_t)c.tile_bytes + (size_t)c.htile_bytes + (size_t)a.H * c.chk * 8 +
-               (size_t)a.H * 8;
-  if (pl.col_lds > (size_t)afno::kLdsBytes)
+  if (column_lds_limit(c) > (size_t)afno::kLdsBytes)
     return fail(AFNO_ERR_UNSUPPORTED, "column tile (H x block size) does not fit in LDS");
-  if (!passes_fit(c.rh, pl.col_threads / c.chk, afno::kColEmax))
-    return fail(AFNO_ERR_UNSUPPORTED, "H transform exceeds the per-thread register budget");
+  afno::plan_general_column(pl);
 
   pl.spec_bytes = (size_t)a.B * a.H * pl.KW * a.C * 2 * es;
   pl.frag_offset = (pl.spec_bytes + 255) / 256 * 256;
   const bool mfma = afno::use_mfma_col(pl);
   const bool hid = afno::use_mfma_hidden(pl);
+  const bool general = !mfma && !hid && !afno::use_fast_col(pl);
   const size_t fb = hid ? afno::hidden_frag_bytes(pl)
-                        : ((mfma || afno::use_fast_col(pl)) ? afno::frag_bytes(pl) : 0);
+                        : (general ? afno::general_frag_bytes(pl, 2) : afno::frag_bytes(pl));
+  pl.plain_words = false;
   pl.tab_offset = (pl.frag_offset + fb + 255) / 256 * 256;
   pl.ws_bytes = (mfma || hid) ? pl.tab_offset + afno::fwd_tab_bytes(pl) : pl.frag_offset + fb;
 
@@ -280,6 +282,12 @@ int run(const Args& a, int stage, float* dst, hipStream_t stream, bool noalloc =
   afno::Plan pl;
   int rc = make_plan(a, pl);
   if (rc != AFNO_OK || a.B == 0) return rc;
+  // the size-generic column kernel can do without prepared words: they are no reason to refuse
+  if (noalloc && pl.ws_bytes > kScratchBytes && !afno::use_mfma_col(pl) &&
+      !afno::use_mfma_hidden(pl) && !afno::use_fast_col(pl)) {
+    pl.plain_words = true;
+    pl.ws_bytes = pl.spec_bytes;
+  }
   if (noalloc && pl.KW > 0 && pl.ws_bytes > kScratchBytes)
     return fail(AFNO_ERR_UNSUPPORTED, "the workspace of " + std::to_string(pl.ws_bytes) +
                                           " bytes exceeds the " + std::to_string(kScratchBytes) +
@@ -354,7 +362,11 @@ int run_backward(const Args& a, const void* gout, float* dw1, float* db1, float*
       if (&q != &o && q.p && q.n && overlaps(o.p, o.n, q.p, q.n))
         return fail(AFNO_ERR_ALIAS, "two outputs overlap");
   }
-  if (a.B > 0 && afno::bwd_lds(pl) > (size_t)afno::kLdsBytes)
+  // (the limit counts two bit masks of the column beside the forward's column_lds_limit)
+  const size_t bwd_lds = afno::use_mfma_col(pl) ? afno::bwd_mfma_lds(pl)
+                             : column_lds_limit(pl.col) +
+                                   2 * (((size_t)pl.col.H16 * (2 * pl.bs / 32) * 4 + 15) / 16 * 16);
+  if (a.B > 0 && bwd_lds > (size_t)afno::kLdsBytes)
     return fail(AFNO_ERR_UNSUPPORTED, "backward column tile (H x block size) does not fit in LDS");
 
   std::call_once(g_attr_once, [] {
@@ -375,7 +387,7 @@ int run_backward(const Args& a, const void* gout, float* dw1, float* db1, float*
   pl.bwd.sx_offset = 0;
   pl.bwd.sg_offset = up(pl.spec_bytes);
   pl.bwd.wt_offset = pl.bwd.sg_offset + up(pl.spec_bytes);
-  pl.bwd.prep_offset = pl.bwd.wt_offset + up(2 * wb);
+  pl.bwd.prep_offset = pl.bwd.wt_offset + (afno::use_mfma_col(pl) ? up(2 * wb) : 0);
   pl.bwd.modes_offset = pl.bwd.prep_offset + up(afno::bwd_prep_bytes(pl));
   const size_t modes_bytes = (size_t)4 * a.nb * 2 * pl.bs * (size_t)afno::bwd_mpad(pl) * es;
   pl.bwd.acc_offset = pl.bwd.modes_offset + up(modes_bytes);

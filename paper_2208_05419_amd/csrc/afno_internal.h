@@ -11,9 +11,7 @@ namespace afno {
 constexpr int kRowThreads = 256;      // threads of a W-axis workgroup
 constexpr int kRowEmax = 32;          // complex values a thread holds in a W pass
 constexpr int kRowLdsMax = 160 * 1024; // LDS budget of a W-axis workgroup
-constexpr int kColEmax = 24;          // complex values a thread holds in an H pass
 constexpr int kColMaxMTiles = 12;     // 16-row MFMA tiles per column: H <= 192
-constexpr int kColMaxThreads = 512;   // 8 waves: bs <= 128
 constexpr int kLdsBytes = 160 * 1024; // LDS of one gfx950 CU
 
 // profile events per timed call: before the first kernel and after each of the four
@@ -37,11 +35,17 @@ struct ColParams {
   int ldt;            // LDS row stride of the column tile, elements
   int ldh;            // LDS row stride of the hidden tile (hs != bs), elements
   int htile_bytes;    // the hidden tile (0 when hs = bs)
-  int chk;            // channels per pass of the H transform
   int kept_h;
   int tile_bytes;
   float lam, inv_sqrt_h;
-  Radices rh;
+  // the size-generic kernels (plan_general_column)
+  int n1, n2;         // H = n1 n2
+  int chk;            // channels per chunk of the H transforms
+  int chk_inv;        // ceil(2^20 / chk): t / chk = (t chk_inv) >> 20 for t < 1024
+  int threads;
+  int wm, wn, mw, nw; // wave grid of the products: wm x wn waves of mw row by nw entry tiles
+  int mt;             // row tiles of 16 with a kept row
+  uint64_t mlist;     // their indices, four bits each
 };
 
 struct Plan {
@@ -53,11 +57,11 @@ struct Plan {
   RowParams row;
   ColParams col;
   size_t row_lds, col_lds;
-  int col_threads;
   size_t spec_bytes;  // spectrum: B * H * KW * C complex values
-  size_t frag_offset; // fragment-ordered weights (size-specialised column kernels), after S
+  size_t frag_offset; // fragment-ordered weights, after S
   size_t tab_offset;  // transform table (MFMA-transform column kernel), after the weights
   size_t ws_bytes;    // whole workspace
+  bool plain_words;   // no room for prepared words: the size-generic kernel gathers the weights
   struct {            // backward-pass workspace offsets (afno_filter_backward)
     size_t sx_offset, sg_offset, wt_offset, prep_offset, modes_offset, acc_offset, bytes;
   } bwd;
@@ -79,6 +83,9 @@ struct BlockPtrs {
   size_t t_off, u_off, v_off, w_off, h_off, wat_off, wbt_off, s_off;
 };
 
+// the size-generic column kernels' split of H, wave grid, chunk and LDS (pl.col, pl.col_lds)
+void plan_general_column(Plan& pl);
+size_t general_frag_bytes(const Plan& pl, int nmat);
 hipError_t set_kernel_attributes();
 // 0: specialised kernels where available, 1: generic only, 2: as 0 without the
 // MFMA-transform column kernel
@@ -95,9 +102,10 @@ size_t frag_bytes(const Plan& pl);
 size_t mfma_tab_bytes(const Plan& pl);
 size_t fwd_tab_bytes(const Plan& pl);   // the forward's tables (kept-row kernel included)
 // ev: NULL, or kProfEvents events recorded before the first kernel and after each phase
-// backward pass: modes per block of the per-mode factor tensors, and the column kernel's LDS
+// backward pass: modes per block of the per-mode factor tensors, and the matrix-core column
+// kernel's LDS
 int64_t bwd_mpad(const Plan& pl);
-size_t bwd_lds(const Plan& pl);
+size_t bwd_mfma_lds(const Plan& pl);
 size_t bwd_prep_bytes(const Plan& pl);  // prepared operands of the matrix-core backward
 size_t bwd_acc_floats(const Plan& pl);  // fp32 sums of the weight and bias gradients
 int wgrad_slab_chunks(const Plan& pl, int* kchunk);

@@ -62,8 +62,9 @@ size_t hidden_frag_bytes(const Plan& pl);
 // tasks of the preparation job: the fragment-ordered weights' words (hidden = true: the
 // hidden-size kernel's), and the DFT table's columns if with_tab
 static int64_t prep_words_host(const Plan& pl, bool with_tab, int kept_h, int kp = 0,
-                               bool hidden = false) {
+                               bool hidden = false, int general = 0) {
   const int hp = mfma_col_hp(pl.H);
+  if (general) return (int64_t)general_frag_bytes(pl, general) / 16;
   if (hidden) return (int64_t)hidden_frag_bytes(pl) / 16 + (with_tab ? 2 * hp : 0);
   return pl.nb * (pl.dtype == 0 ? frag_words_per_block<float>((int)pl.bs)
                                 : frag_words_per_block<bf16>((int)pl.bs)) +
@@ -226,6 +227,67 @@ bool use_fast_col(const Plan& pl) {
          fast_col_available(pl.dtype, pl.H, pl.bs);
 }
 
+size_t general_frag_bytes(const Plan& pl, int nmat) {
+  return (size_t)general_words((int)pl.nb, (int)pl.bs, pl.col.hs, nmat, pl.dtype == 0 ? 4 : 2) * 16;
+}
+
+// H = n1 n2, as balanced as the kernels' two sets of register DFTs allow (n1 <= n2)
+static bool col_split(int H, int& n1, int& n2) {
+#define AFNO_CASE(N) || n == N
+  auto in1 = [](int n) { return false AFNO_COL_N1(AFNO_CASE); };
+  auto in2 = [](int n) { return false AFNO_COL_N2(AFNO_CASE) AFNO_COL_N2_BIG(AFNO_CASE); };
+#undef AFNO_CASE
+  for (n1 = 12; n1 >= 1; --n1) {
+    n2 = H / n1;
+    if (H % n1 == 0 && n1 <= n2 && in1(n1) && in2(n2)) return true;
+  }
+  return false;
+}
+
+void plan_general_column(Plan& pl) {
+  ColParams& c = pl.col;
+  const int es = pl.dtype == 0 ? 4 : 2;
+  (void)col_split(c.H, c.n1, c.n2);  // every 5-smooth H <= 192 splits
+  // row tiles with a kept row
+  c.mt = 0;
+  c.mlist = 0;
+  for (int t = 0; t < c.H16 / 16; ++t) {
+    bool any = false;
+    for (int r = 16 * t; r < 16 * t + 16 && r < c.H; ++r) {
+      const int s = r <= c.H / 2 ? r : c.H - r;
+      any = any || s < c.kept_h;
+    }
+    if (any) c.mlist |= (uint64_t)t << (4 * c.mt++);
+  }
+  // Wave grid: four entry tiles a wave where the sizes allow (a row fragment from LDS then
+  // feeds four products), about eight waves, at most eight tiles a wave; 16 where that would
+  // take more than 12 waves.
+  c.nw = c.bs % 32 == 0 && c.hs % 32 == 0 && c.bs >= 64 ? 4 : 2;
+  c.wn = c.bs / (8 * c.nw);
+  const int mt = std::max(c.mt, 1);
+  for (int mw_max : {8 / c.nw, c.nw == 4 ? 4 : 6}) {
+    c.wm = std::max((mt + mw_max - 1) / mw_max, std::min(mt, std::max(1, 8 / c.wn)));
+    c.mw = (mt + c.wm - 1) / c.wm;
+    if (c.mw == 5) c.mw = 6;
+    c.wm = (mt + c.mw - 1) / c.mw;
+    if (c.wm * c.wn <= 12) break;
+  }
+  // Chunk of the transforms: one task a thread, so chk n2 threads; the most channels with which
+  // two workgroups fit a compute unit (80 KB, 512 threads: 60 x 48 bf16 57 us at 48, 88 at 16;
+  // 180 x 64 180 us at 16, 218 at 32, which leaves room for one).  Where even 16 channels leave
+  // room for one workgroup only, the most that fit at all (180 x 128: 214 us at 32, 288 at 16).
+  auto lds = [&](int chk) {
+    return (size_t)c.tile_bytes + c.htile_bytes + (es == 2 ? (size_t)c.H * chk * 8 : 0) + (size_t)c.H * 8;
+  };
+  const int share = lds(16) <= (size_t)kLdsBytes / 2 ? 2 : 1;
+  c.chk = 16;
+  for (int chk = 32; chk <= c.bs; chk += 16)
+    if (c.bs % chk == 0 && chk * c.n2 <= 1024 / share && lds(chk) <= (size_t)kLdsBytes / share) c.chk = chk;
+  c.chk_inv = ((1 << 20) + c.chk - 1) / c.chk;
+  c.threads = 64 * std::max(c.wm * c.wn, (c.chk * c.n2 + 63) / 64);
+  pl.col_lds = lds(c.chk);
+}
+
 size_t frag_bytes(const Plan& pl) {
   return (size_t)pl.nb * (size_t)(pl.dtype == 0 ? frag_words_per_block<float>((int)pl.bs) * 4
                                                  : frag_words_per_block<bf16>((int)pl.bs) * 16);
@@ -241,7 +303,9 @@ static hipError_t launch_all(const Plan& pl, const void* x, const void* w1, cons
   const bool row_fast = !generic && fast_row_available(pl.W, pl.C);
   const bool col_mfma = use_mfma_col(pl);
   const bool col_fast = use_fast_col(pl);
-  const bool col_hid = use_mfma_hidden(pl);
+  const int col_stage = (stage == kStageSpectrum) ? 1 : (stage == kStageMixed ? 2 : 0);
+  const bool col_hid = use_mfma_hidden(pl) && col_stage == 0;
+  const bool col_gen = !col_mfma && !col_fast && !col_hid;
   dim3 rgrid((unsigned)(pl.B * pl.H), (unsigned)(pl.C / pl.row.rc));
   // prepared column-kernel operands (after the spectrum in the workspace; independent of x):
   // extra workgroups of the size-specialised W-axis forward launch, else a launch of their own
@@ -253,13 +317,18 @@ static hipError_t launch_all(const Plan& pl, const void* x, const void* w1, cons
   if (col_mfma || (sizeof(T) == 2 && col_hid))
     pj.tout = reinterpret_cast<uint4*>(static_cast<char*>(S) + pl.tab_offset);
   if (sizeof(T) == 2 && col_hid) pj.hs = (int)pl.col.hs;  // the hidden-size kernel's fragments
+  if (col_gen && !pl.plain_words) {
+    pj.wout = reinterpret_cast<typename FragWord<T>::type*>(static_cast<char*>(S) + pl.frag_offset);
+    pj.general = 2;
+    pj.hs = (int)pl.col.hs;
+  }
   // ev[0]: recorded only before a preparation launch of its own (a preparation inside the W-axis
   // forward launch belongs to that phase; the profile counts an unrecorded ev[0] as zero)
   const bool prep_launch = pj.wout && !row_fast;
   if (ev && prep_launch) (void)hipEventRecord(ev[0], st);
   if (prep_launch) {
     const unsigned g = (unsigned)std::min<int64_t>(
-        (prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0) + 255) / 256, 4096);
+        (prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0, pj.general) + 255) / 256, 4096);
     hipLaunchKernelGGL(prep_operands_kernel<T>, dim3(g), dim3(256), 0, st, pj);
   }
   hipError_t e = hipGetLastError();
@@ -267,27 +336,38 @@ static hipError_t launch_all(const Plan& pl, const void* x, const void* w1, cons
   if (ev) (void)hipEventRecord(ev[1], st);
   if (row_fast)
     launch_row_fwd_fast<T>(pl, xt, St, pj,
-                           prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0), st);
+                           prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0, pj.general), st);
   else
     hipLaunchKernelGGL(row_r2c_kernel<T>, rgrid, dim3(kRowThreads), pl.row_lds, st, xt, St, pl.row);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[2], st);
-  const int col_stage = (stage == kStageSpectrum) ? 1 : (stage == kStageMixed ? 2 : 0);
   if (col_mfma) {
     if constexpr (sizeof(T) == 2)
       launch_col_mfma(pl, St, static_cast<const bf16*>(b1), static_cast<const bf16*>(b2),
                       col_stage, st);
-  } else if (col_hid && col_stage == 0) {
+  } else if (col_hid) {
     if constexpr (sizeof(T) == 2)
       launch_col_mfma_hidden(pl, St, static_cast<const bf16*>(b1), static_cast<const bf16*>(b2), st);
   } else if (col_fast)
     launch_col_fast<T>(pl, St, static_cast<const T*>(b1), static_cast<const T*>(b2), col_stage, st);
-  else
-    hipLaunchKernelGGL(column_kernel<T>, dim3((unsigned)(pl.B * pl.KW * pl.nb)),
-                       dim3(pl.col_threads), pl.col_lds, st, St, static_cast<const T*>(w1),
-                       static_cast<const T*>(b1), static_cast<const T*>(w2),
-                       static_cast<const T*>(b2), pl.col, col_stage);
+  else {
+    const dim3 grid((unsigned)(pl.B * pl.KW * pl.nb)), block(pl.col.threads);
+    const uint4* wf = reinterpret_cast<const uint4*>(static_cast<char*>(S) + pl.frag_offset);
+    const T *B1 = static_cast<const T*>(b1), *B2 = static_cast<const T*>(b2);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, pl.col_lds, st, St, wf, static_cast<const T*>(w1),
+                         static_cast<const T*>(w2), B1, B2, pl.col, col_stage);
+    };
+    if (pl.plain_words)
+      launch(column_general<T, kSizesAll, true, true>);
+    else if (pl.col.n2 > 16)
+      launch(column_general<T, kSizesBig, true, false>);
+    else if (pl.col.mw * pl.col.nw > 8)
+      launch(column_general<T, kSizesMain, true, false>);
+    else
+      launch(column_general<T, kSizesMain, false, false>);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[3], st);
@@ -317,21 +397,20 @@ bool use_mfma_bwd(const Plan& pl) { return use_mfma_col(pl); }
 
 int64_t bwd_mpad(const Plan& pl) { return pl.B * pl.KW * (int64_t)col_bwd_hc((int)pl.col.H16); }
 
-size_t bwd_lds(const Plan& pl) {
-  if (use_mfma_bwd(pl)) {
-    const int hp = mfma_col_hp(pl.H);
+size_t bwd_mfma_lds(const Plan& pl) {
+  const int hp = mfma_col_hp(pl.H);
 #define AFNO_CASE(HP_, BS_) \
-    if (hp == HP_ && pl.bs == BS_) return (size_t)MfmaBwd<HP_, BS_>::kBytes;
-    AFNO_MFMA_COL_LIST(AFNO_CASE)
+  if (hp == HP_ && pl.bs == BS_) return (size_t)MfmaBwd<HP_, BS_>::kBytes;
+  AFNO_MFMA_COL_LIST(AFNO_CASE)
 #undef AFNO_CASE
-  }
-  return col_bwd_lds(pl.col);
+  return 0;
 }
 
-// workspace bytes of the prepared operands of the matrix-core backward column kernel: the
-// forward and the backward weight fragments, the DFT table and its rounding remainders
+// workspace bytes of the backward column kernel's prepared operands.  Matrix-core kernel: the
+// forward and the backward weight fragments, the DFT table and its rounding remainders;
+// size-generic kernel: the words of four matrices
 size_t bwd_prep_bytes(const Plan& pl) {
-  if (!use_mfma_bwd(pl)) return 0;
+  if (!use_mfma_bwd(pl)) return general_frag_bytes(pl, 4);
   return 2 * frag_bytes(pl) + 2 * mfma_tab_bytes(pl);
 }
 
@@ -378,13 +457,17 @@ size_t bwd_acc_floats(const Plan& pl) {
   return (size_t)nchunk * 2 * pl.nb * nb2 * (nb2 + 1);
 }
 
-// The W-axis forward transform of x into S (no operand preparation).
+// The W-axis forward transform of x into S, with pj's preparation if pj.wout is set.
 template <typename T>
-static hipError_t launch_row_forward(const Plan& pl, const T* x, T* S, hipStream_t st) {
+static hipError_t launch_row_forward(const Plan& pl, const T* x, T* S, const PrepJob<T>& pj,
+                                     hipStream_t st) {
+  const int64_t ntask = prep_words_host(pl, false, -1, 0, false, pj.general);
   if (pl.path != 1 && fast_row_available(pl.W, pl.C)) {
-    PrepJob<T> pj{nullptr, nullptr, nullptr, nullptr, (int)pl.nb, (int)pl.bs, (int)pl.H, 0, 0, -1, 0};
-    launch_row_fwd_fast<T>(pl, x, S, pj, 0, st);
+    launch_row_fwd_fast<T>(pl, x, S, pj, ntask, st);
   } else {
+    if (pj.wout)
+      hipLaunchKernelGGL(prep_operands_kernel<T>, dim3((unsigned)std::min<int64_t>((ntask + 255) / 256, 4096)),
+                         dim3(256), 0, st, pj);
     dim3 rgrid((unsigned)(pl.B * pl.H), (unsigned)(pl.C / pl.row.rc));
     hipLaunchKernelGGL(row_r2c_kernel<T>, rgrid, dim3(kRowThreads), pl.row_lds, st, x, S, pl.row);
   }
@@ -428,14 +511,15 @@ static hipError_t launch_bwd(const Plan& pl, const BwdPtrs& a, hipStream_t st) {
   float* bsums = acc + (int64_t)nchunk * 2 * nb * nb2 * nb2;
   const int64_t mpad = bwd_mpad(pl);
   const bool mfma = use_mfma_bwd(pl);
-  hipError_t e = launch_row_forward<T>(pl, x, Sx, st);
-  if (e == hipSuccess) e = launch_row_forward<T>(pl, g, Sg, st);
+  // the size-generic column kernel's words: extra workgroups of the first W-axis launch
+  PrepJob<T> pj{static_cast<const T*>(a.w1), static_cast<const T*>(a.w2), nullptr, nullptr, nb, bs,
+                (int)pl.H, 0, 0, -1, 0, bs, 4};
+  if (!mfma) pj.wout = reinterpret_cast<typename FragWord<T>::type*>(ws + pl.bwd.prep_offset);
+  hipError_t e = launch_row_forward<T>(pl, x, Sx, pj, st);
+  pj.wout = nullptr;
+  if (e == hipSuccess) e = launch_row_forward<T>(pl, g, Sg, pj, st);
   if (e != hipSuccess) return e;
   const int64_t nw = (int64_t)2 * nb * bs * bs;
-  if (!mfma)
-    hipLaunchKernelGGL(conj_transpose_weights<T>, dim3((unsigned)std::min<int64_t>((nw + 255) / 256, 4096)),
-                       dim3(256), 0, st, static_cast<const T*>(a.w1), static_cast<const T*>(a.w2),
-                       wt1, wt2, nb, bs);
   if constexpr (sizeof(T) == 2) {
     if (mfma) {
       typedef typename FragWord<T>::type Word;
@@ -464,11 +548,21 @@ static hipError_t launch_bwd(const Plan& pl, const BwdPtrs& a, hipStream_t st) {
                           static_cast<const T*>(a.b2), modes, mpad, st);
     }
   }
-  if (!mfma)
-    hipLaunchKernelGGL(column_bwd_kernel<T>, dim3((unsigned)(pl.B * pl.KW * pl.nb)),
-                       dim3(pl.col_threads), bwd_lds(pl), st, Sx, Sg, static_cast<const T*>(a.w1),
-                       static_cast<const T*>(a.b1), static_cast<const T*>(a.w2),
-                       static_cast<const T*>(a.b2), wt1, wt2, pl.col, modes, mpad, (int)pl.W);
+  if (!mfma) {
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.B * pl.KW * pl.nb)), dim3(pl.col.threads),
+                         pl.col_lds, st, Sx, Sg,
+                         reinterpret_cast<const uint4*>(ws + pl.bwd.prep_offset),
+                         static_cast<const T*>(a.b1), static_cast<const T*>(a.b2), pl.col, modes,
+                         mpad, (int)pl.W);
+    };
+    if (pl.col.n2 > 16)
+      launch(column_bwd_general<T, kSizesBig, true>);
+    else if (pl.col.mw * pl.col.nw > 8)
+      launch(column_bwd_general<T, kSizesMain, true>);
+    else
+      launch(column_bwd_general<T, kSizesMain, false>);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // dx = g + C2R(Sg): the W-axis inverse with g as the residual, first, while the gradient
@@ -584,10 +678,17 @@ hipError_t set_kernel_attributes() {
   AFNO_ATTR(row_r2c_kernel<bf16>)
   AFNO_ATTR(row_c2r_kernel<float>)
   AFNO_ATTR(row_c2r_kernel<bf16>)
-  AFNO_ATTR(column_kernel<float>)
-  AFNO_ATTR(column_kernel<bf16>)
-  AFNO_ATTR(column_bwd_kernel<float>)
-  AFNO_ATTR(column_bwd_kernel<bf16>)
+#define AFNO_CASE(T)                                      \
+  AFNO_ATTR((column_general<T, kSizesMain, false, false>)) \
+  AFNO_ATTR((column_general<T, kSizesMain, true, false>))  \
+  AFNO_ATTR((column_general<T, kSizesBig, true, false>))   \
+  AFNO_ATTR((column_general<T, kSizesAll, true, true>))    \
+  AFNO_ATTR((column_bwd_general<T, kSizesMain, false>))    \
+  AFNO_ATTR((column_bwd_general<T, kSizesMain, true>))     \
+  AFNO_ATTR((column_bwd_general<T, kSizesBig, true>))
+  AFNO_CASE(float)
+  AFNO_CASE(bf16)
+#undef AFNO_CASE
   AFNO_ATTR((gemm_bf16<kEpiGelu, 128>))
   AFNO_ATTR((gemm_bf16<kEpiResidual, 128>))
   AFNO_ATTR(wgrad_slab<64>)

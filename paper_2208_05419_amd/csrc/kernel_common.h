@@ -29,6 +29,15 @@ union V16 {
   bf16 h[8];
 };
 
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+typedef bf16 bf16x2v __attribute__((ext_vector_type(2)));
+// two floats -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32
+__device__ __forceinline__ uint32_t cvt_pk(float lo, float hi) {
+  union { bf16x2v v; uint32_t u; } w;
+  w.v = __builtin_convertvector((f32x2v){lo, hi}, bf16x2v);
+  return w.u;
+}
+
 // One complex value (re, im) in storage type T.
 __device__ __forceinline__ float2 ld_c(const float* p) { return *reinterpret_cast<const float2*>(p); }
 __device__ __forceinline__ float2 ld_c(const bf16* p) {
@@ -38,10 +47,7 @@ __device__ __forceinline__ float2 ld_c(const bf16* p) {
 }
 __device__ __forceinline__ void st_c(float* p, float2 v) { *reinterpret_cast<float2*>(p) = v; }
 __device__ __forceinline__ void st_c(bf16* p, float2 v) {
-  union { uint32_t u; bf16 h[2]; } w;
-  w.h[0] = (bf16)v.x;
-  w.h[1] = (bf16)v.y;
-  *reinterpret_cast<uint32_t*>(p) = w.u;
+  *reinterpret_cast<uint32_t*>(p) = cvt_pk(v.x, v.y);
 }
 // Two complex values (4 T) in one access.
 __device__ __forceinline__ float4 ld_c2(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -52,9 +58,7 @@ __device__ __forceinline__ float4 ld_c2(const bf16* p) {
 }
 __device__ __forceinline__ void st_c2(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
 __device__ __forceinline__ void st_c2(bf16* p, float4 v) {
-  union { uint2 u; bf16 h[4]; } w;
-  w.h[0] = (bf16)v.x; w.h[1] = (bf16)v.y; w.h[2] = (bf16)v.z; w.h[3] = (bf16)v.w;
-  *reinterpret_cast<uint2*>(p) = w.u;
+  *reinterpret_cast<uint2*>(p) = make_uint2(cvt_pk(v.x, v.y), cvt_pk(v.z, v.w));
 }
 
 // MFMA operand types per storage dtype.
@@ -205,10 +209,7 @@ __device__ __forceinline__ float2 unpack_c(uint32_t v, const bf16*) {
   return make_float2(__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u));
 }
 __device__ __forceinline__ uint32_t pack_c(float2 z, const bf16*) {
-  union { uint32_t u; bf16 h[2]; } w;
-  w.h[0] = (bf16)z.x;
-  w.h[1] = (bf16)z.y;
-  return w.u;
+  return cvt_pk(z.x, z.y);
 }
 
 // An opaque copy of a value: expressions of the copy cannot be tied to expressions of the

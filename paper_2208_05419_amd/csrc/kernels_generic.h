@@ -1,7 +1,7 @@
-// kernels_generic.h -- size-generic kernels of the AFNO filter: any H, W of the form
+// kernels_generic.h -- size-generic W-axis kernels of the AFNO filter: any W of the form
 // 2^a 3^b 5^c within the plan limits.  Transforms run as radix-2/3/4/5 Stockham passes
 // over LDS (fft_lds.h); the size-specialised kernels of kernels_fast.h replace them for
-// the grids the filter is usually run on.
+// widths from 12 to 576.  The size-generic column kernels are in kernels_column.h.
 //
 // Three passes over HBM, all on one spectrum workspace S [B][H][KW][C] (complex,
 // (re, im) interleaved, stored in the filter's dtype; KW = kept_w columns):
@@ -161,197 +161,6 @@ row_c2r_kernel(const T* __restrict__ S, const T* __restrict__ x, T* __restrict__
       else ov.h[e] = (bf16)((float)xv.h[e] + y[e]);
     }
     *reinterpret_cast<uint4*>(out + off) = ov.u;
-  }
-}
-
-// ------------------------------------------------------------------ kernel 2: column
-
-// One layer of the block MLP on the LDS tile: acc[m][n] = tile rows x Wexp for the
-// wave's two 16-column output tiles, over the live row tiles.
-template <typename T>
-__device__ __forceinline__ void block_gemm(const T* tile, int ldt, const T* w, int n_out,
-                                           int n_in, int mt, uint32_t live, int wave, int lane,
-                                           f32x4 (&acc)[kColMaxMTiles][2]) {
-  typedef Mma<T> M;
-#pragma unroll
-  for (int m = 0; m < kColMaxMTiles; ++m)
-    for (int n = 0; n < 2; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int jn0 = (32 * wave + (lane & 15)) >> 1;  // complex output column of tile 0
-  const int jn1 = jn0 + 8;
-  const int sg = lane & 1;
-  for (int kb = 0; kb < 2 * n_in; kb += M::kK) {
-    const typename M::Frag b0 = M::load_b(w, n_out, kb, jn0, sg, lane);
-    const typename M::Frag b1 = M::load_b(w, n_out, kb, jn1, sg, lane);
-#pragma unroll
-    for (int m = 0; m < kColMaxMTiles; ++m) {
-      if (m < mt && ((live >> m) & 1u)) {
-        const typename M::Frag a = M::load_a(tile + (16 * m + (lane & 15)) * ldt, kb, lane);
-        acc[m][0] = M::mma(a, b0, acc[m][0]);
-        acc[m][1] = M::mma(a, b1, acc[m][1]);
-      }
-    }
-  }
-}
-
-// grid B * KW * nb, block 64 * min(8, max(max(bs, hs) / 16, 4)).  stage: 0 full, 1 stop after
-// the forward transform, 2 stop after the MLP.  hs != bs: the hidden layer (2 hs real entries
-// per row) has its own LDS tile after the column tile, and waves take its 32-column groups in
-// turn.
-template <typename T>
-__global__ void __launch_bounds__(kColMaxThreads)
-column_kernel(T* __restrict__ S, const T* __restrict__ w1, const T* __restrict__ b1,
-              const T* __restrict__ w2, const T* __restrict__ b2, ColParams p, int stage) {
-  extern __shared__ float4 smem_raw[];
-  T* tile = reinterpret_cast<T*>(smem_raw);                              // H16 x ldt
-  T* htile = p.htile_bytes ? reinterpret_cast<T*>(reinterpret_cast<char*>(smem_raw) + p.tile_bytes)
-                           : tile;                                       // H16 x ldh
-  float2* fbuf = reinterpret_cast<float2*>(reinterpret_cast<char*>(smem_raw) + p.tile_bytes +
-                                           p.htile_bytes);
-  float2* tw = fbuf + (size_t)p.H * p.chk;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nthr = blockDim.x;
-  const int bs = p.bs, hs = p.hs, ldt = p.ldt, H = p.H, H16 = p.H16;
-  const int ldh = p.htile_bytes ? p.ldh : ldt;
-
-  const int blk = blockIdx.x % p.nb;  // consecutive workgroups -> different XCDs -> blocks
-  const int rest = blockIdx.x / p.nb;
-  const int kw = rest % p.KW;
-  const int64_t b = rest / p.KW;
-
-  make_twiddles(tw, H);
-
-  // ---- load the column tile: rows h < H of S[b][h][kw][blk*bs : +bs], zero padding rows
-  constexpr int V = Store<T>::kVec;
-  const int vpr = 2 * bs / V;
-  const int64_t row_stride = (int64_t)p.KW * p.C * 2;
-  T* col = S + ((b * H) * p.KW + kw) * (int64_t)p.C * 2 + (int64_t)blk * bs * 2;
-  for (int it = tid; it < H16 * vpr; it += nthr) {
-    const int h = it / vpr, cv = it - h * vpr;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (h < H) v = *reinterpret_cast<const uint4*>(col + h * row_stride + cv * V);
-    *reinterpret_cast<uint4*>(tile + h * ldt + cv * V) = v;
-  }
-  __syncthreads();
-
-  const int chk = p.chk;
-  const int sig = tid % chk, sub = tid / chk, nsub = nthr / chk;
-  const float sch = p.inv_sqrt_h;
-
-  // ---- forward DFT along H, chk channels at a time through the float32 buffer
-  for (int cc = 0; cc < bs; cc += chk) {
-    for (int it = tid; it < H * chk; it += nthr) {
-      const int h = it / chk, q = it - h * chk;
-      const T* e = tile + h * ldt + 2 * (cc + q);
-      fbuf[h * chk + q] = make_float2(ld_f(e), ld_f(e + 1));
-    }
-    __syncthreads();
-    fft_lds<kColEmax, false>(fbuf, chk, p.rh, sig, sub, nsub, tw);
-    for (int it = tid; it < H * chk; it += nthr) {
-      const int h = it / chk, q = it - h * chk;
-      const float2 z = fbuf[h * chk + q];
-      T* e = tile + h * ldt + 2 * (cc + q);
-      e[0] = Store<T>::to(z.x * sch);
-      e[1] = Store<T>::to(z.y * sch);
-    }
-    __syncthreads();
-  }
-
-  if (stage != 1) {
-    // ---- block MLP.  A wave owns 32 real output columns (16 complex) at a time.
-    const int mt = H16 / 16;
-    uint32_t live = 0;
-    for (int m = 0; m < mt; ++m) {
-      bool any = false;
-      for (int r = 16 * m; r < 16 * m + 16; ++r) any |= row_kept(r, H, p.kept_h);
-      live |= (any ? 1u : 0u) << m;
-    }
-    const T* W1 = w1 + (int64_t)blk * bs * hs * 2;
-    const T* W2 = w2 + (int64_t)blk * hs * bs * 2;
-    const T* B1 = b1 + (int64_t)blk * hs * 2;
-    const T* B2 = b2 + (int64_t)blk * bs * 2;
-    const int nwaves = nthr / 64;
-    f32x4 acc[kColMaxMTiles][2];
-
-    // layer 1: hidden groups grp = wave, wave + nwaves, ...; in place (hs = bs: one group per
-    // wave at most) the spectrum rows are read by every wave before any is overwritten
-    const int ng1 = hs / 16;
-    const int rounds = (ng1 + nwaves - 1) / nwaves;
-    for (int rd = 0; rd < rounds; ++rd) {
-      const int grp = wave + rd * nwaves;
-      const bool act = grp < ng1;
-      if (act) block_gemm<T>(tile, ldt, W1, hs, bs, mt, live, grp, lane, acc);
-      if (htile == tile) __syncthreads();
-      if (act) {
-        const int nu = 32 * grp + (lane & 15);
-        const float bia0 = ld_f(B1 + nu), bia1 = ld_f(B1 + nu + 16);
-#pragma unroll
-        for (int m = 0; m < kColMaxMTiles; ++m) {
-          if (m < mt && ((live >> m) & 1u)) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int row = 16 * m + 4 * (lane >> 4) + r;
-              htile[row * ldh + nu] = Store<T>::to(fmaxf(acc[m][0][r] + bia0, 0.f));
-              htile[row * ldh + nu + 16] = Store<T>::to(fmaxf(acc[m][1][r] + bia1, 0.f));
-            }
-          }
-        }
-      }
-    }
-    __syncthreads();  // hidden layer complete
-    const bool active = wave < bs / 16;
-    const int nu0 = 32 * wave + (lane & 15);  // real output column of tile 0 (tile 1: +16)
-    if (active) block_gemm<T>(htile, ldh, W2, bs, hs, mt, live, wave, lane, acc);
-    __syncthreads();  // every wave has read the hidden rows
-    if (active) {
-      const float bia0 = ld_f(B2 + nu0), bia1 = ld_f(B2 + nu0 + 16);
-      const float lam = p.lam;
-#pragma unroll
-      for (int m = 0; m < kColMaxMTiles; ++m) {
-        if (m < mt) {
-          const bool lv = (live >> m) & 1u;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int row = 16 * m + 4 * (lane >> 4) + r;
-            const bool keep = lv && row_kept(row, H, p.kept_h);
-            float o0 = lv ? acc[m][0][r] + bia0 : 0.f;
-            float o1 = lv ? acc[m][1][r] + bia1 : 0.f;
-            o0 = o0 > lam ? o0 - lam : (o0 < -lam ? o0 + lam : 0.f);
-            o1 = o1 > lam ? o1 - lam : (o1 < -lam ? o1 + lam : 0.f);
-            tile[row * ldt + nu0] = Store<T>::to(keep ? o0 : 0.f);
-            tile[row * ldt + nu0 + 16] = Store<T>::to(keep ? o1 : 0.f);
-          }
-        }
-      }
-    }
-    __syncthreads();
-
-    if (stage == 0) {
-      // ---- inverse DFT along H
-      for (int cc = 0; cc < bs; cc += chk) {
-        for (int it = tid; it < H * chk; it += nthr) {
-          const int h = it / chk, q = it - h * chk;
-          const T* e = tile + h * ldt + 2 * (cc + q);
-          fbuf[h * chk + q] = make_float2(ld_f(e), ld_f(e + 1));
-        }
-        __syncthreads();
-        fft_lds<kColEmax, true>(fbuf, chk, p.rh, sig, sub, nsub, tw);
-        for (int it = tid; it < H * chk; it += nthr) {
-          const int h = it / chk, q = it - h * chk;
-          const float2 z = fbuf[h * chk + q];
-          T* e = tile + h * ldt + 2 * (cc + q);
-          e[0] = Store<T>::to(z.x * sch);
-          e[1] = Store<T>::to(z.y * sch);
-        }
-        __syncthreads();
-      }
-    }
-  }
-
-  // ---- store the tile back in place
-  for (int it = tid; it < H * vpr; it += nthr) {
-    const int h = it / vpr, cv = it - h * vpr;
-    *reinterpret_cast<uint4*>(col + h * row_stride + cv * V) =
-        *reinterpret_cast<const uint4*>(tile + h * ldt + cv * V);
   }
 }
 

@@ -73,14 +73,6 @@ __device__ __forceinline__ bf16x8 as_frag(uint4 u) {
 __device__ __forceinline__ uint4 xor4(uint4 u, uint32_t m) {
   return make_uint4(u.x ^ m, u.y ^ m, u.z ^ m, u.w ^ m);
 }
-typedef float f32x2v __attribute__((ext_vector_type(2)));
-typedef bf16 bf16x2v __attribute__((ext_vector_type(2)));
-// two floats -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32
-__device__ __forceinline__ uint32_t cvt_pk(float lo, float hi) {
-  union { bf16x2v v; uint32_t u; } w;
-  w.v = __builtin_convertvector((f32x2v){lo, hi}, bf16x2v);
-  return w.u;
-}
 __device__ __forceinline__ f32x4 mma_bf16(uint4 a, uint4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(a), as_frag(b), c, 0, 0, 0);
 }

@@ -189,6 +189,44 @@ __device__ __forceinline__ void prep_hidden_words(int64_t i, int64_t stride, con
   }
 }
 
+// One entry of the real-ified complex weight Wx[2 i + rho][2 j + sg] = (Wr, -Wi ; Wi, Wr)[rho][sg]
+// of w [n_in][n_out][2].
+template <typename T>
+__device__ __forceinline__ T real_entry(const T* w, int n_out, int row, int col) {
+  const T v = w[((int64_t)(row >> 1) * n_out + (col >> 1)) * 2 + ((row ^ col) & 1)];
+  return (row & 1) && !(col & 1) ? (T)-v : v;
+}
+
+// The size-generic column kernels' words (kernels_column.h), tasks i, i + stride, ...: per block
+// W1x (K = 2 bs, N = 2 hs), W2x (K = 2 hs, N = 2 bs) and, with nmat = 4 (hs = bs), W2x^T and
+// W1x^T.  Word ((s N / 16 + t) 64 + lane) of a matrix: entries k = 32 s + 8 g .. + 7 (fp32: 16 s
+// + 4 g .. + 3) of column 16 t + l16, for lane = 16 g + l16.
+__host__ __device__ inline int64_t general_words(int nb, int bs, int hs, int nmat, int es) {
+  return (int64_t)nb * nmat * bs * hs / 4 * es;
+}
+template <typename T>
+__device__ __forceinline__ void prep_general_words(int64_t i, int64_t stride, const T* w1, const T* w2,
+                                                   uint4* wout, int nb, int bs, int hs, int nmat) {
+  constexpr int E = 16 / sizeof(T);  // entries of a word
+  const int64_t per = (int64_t)bs * hs / 4 * sizeof(T);  // words of a matrix
+  for (; i < nb * nmat * per; i += stride) {
+    const int64_t f = i / per;
+    const int u = (int)(i - f * per), mat = (int)(f % nmat);
+    const int64_t blk = f / nmat;
+    const bool second = mat == 1 || mat == 2;  // from w2
+    const T* w = second ? w2 + blk * hs * bs * 2 : w1 + blk * bs * hs * 2;
+    const int n_out = second ? bs : hs;
+    const int nt = (mat < 2 ? 2 * n_out : 2 * bs) / 16;
+    const int lane = u & 63, t = (u >> 6) % nt, s = (u >> 6) / nt;
+    const int k0 = 4 * E * s + E * (lane >> 4), n = 16 * t + (lane & 15);
+    union { uint4 u4; T e[E]; } v;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      v.e[e] = mat < 2 ? real_entry(w, n_out, k0 + e, n) : real_entry(w, n_out, n, k0 + e);
+    wout[i] = v.u4;
+  }
+}
+
 // What to prepare: both layers of every block in fragment order (frag_words_per_block words
 // per block, word ((layer * KSTEPS + s) * NT16 + t) * 64 + lane), then, if tout is set, the
 // DFT table for height H padded to HP: kept_h >= 0, 2 HP column tasks (dft_table_column, the
@@ -205,6 +243,8 @@ struct PrepJob {
   int kept_h;  // the table's rounding, as above
   int kp;      // > 0: the kept-row kernel's two tables for kp kept rows (kept_table_task)
   int hs;      // > 0 and != bs (bf16): the hidden-size kernel's fragments (prep_hidden_words)
+  int general; // > 0: the size-generic column kernels' words instead, this many matrices
+               // (prep_general_words; hs is set; no table)
 };
 
 __host__ __device__ inline int64_t dft_table_tasks(int HP, int kept_h) {
@@ -225,6 +265,11 @@ __device__ __forceinline__ int64_t prep_words(const PrepJob<T>& pj) {
 template <typename T>
 __device__ void prep_operands(int64_t i, int64_t stride, const PrepJob<T>& pj,
                               const float2* roots) {
+  if (pj.general > 0) {
+    prep_general_words<T>(i, stride, pj.w1, pj.w2, reinterpret_cast<uint4*>(pj.wout), pj.nb, pj.bs,
+                          pj.hs, pj.general);
+    return;
+  }
   if constexpr (sizeof(T) == 2) {
     if (pj.hs > 0 && pj.hs != pj.bs) {
       prep_hidden_words(i, stride, pj.w1, pj.w2, pj.wout, pj.tout, pj.nb, pj.bs, pj.hs, pj.H,
