@@ -209,8 +209,10 @@ def _ptr(t):
 
 def _stream(stream):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is None:
+        # the handle of torch's current stream without building a Stream object (2 us a call)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _grid(x, num_blocks: int):

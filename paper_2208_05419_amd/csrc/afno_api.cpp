@@ -261,6 +261,89 @@ hipError_t ws_alloc(void** p, size_t bytes, hipStream_t stream) {
   return hipMallocFromPoolAsync(p, bytes, pool, stream);
 }
 
+// Small workspaces (up to kSlotBytes) come from slots of that pool's memory that the library
+// keeps, at most kSlots (256 MB) a device: a pool allocation and free cost the host 16 us a call,
+// more than the three kernels of a small filter take (16 x 32 x 64: 27 us a call from the pool,
+// 15 from a slot, 11 of them the kernels).  A slot belongs to the stream handle that used it last; it is held by one
+// call while that call enqueues, and every later user first makes its stream wait for the event
+// recorded behind the last one, so that a handle which names another stream by then
+// (hipStreamPerThread in another thread, a destroyed and recreated stream) is ordered all the
+// same.  No slot free for the stream, a larger workspace or a stream under capture (whose graph
+// must own its memory): the pool.
+constexpr size_t kSlotBytes = (size_t)32 << 20;
+constexpr int kSlots = 8;
+struct Slot {
+  void* ptr = nullptr;
+  hipEvent_t done = nullptr;
+  hipStream_t last = nullptr;
+  bool held = false;
+};
+std::mutex g_slot_mu;
+Slot g_slots[kMaxDevices][kSlots];
+
+// One call's workspace.
+struct Workspace {
+  void* ptr = nullptr;
+  Slot* slot = nullptr;
+  hipStream_t stream = nullptr;
+
+  hipError_t acquire(size_t bytes, hipStream_t st) {
+    stream = st;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = -1;
+    if (bytes <= kSlotBytes && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices &&
+        hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+        take_slot(dev))
+      return hipSuccess;
+    (void)hipGetLastError();
+    return ws_alloc(&ptr, bytes, st);
+  }
+  // after the call's last launch
+  hipError_t release() {
+    if (!slot) return hipFreeAsync(ptr, stream);
+    hipError_t e = hipEventRecord(slot->done, stream);
+    if (e != hipSuccess) e = hipStreamSynchronize(stream);  // nothing may still use the slot
+    std::lock_guard<std::mutex> lk(g_slot_mu);
+    slot->held = false;
+    return e;
+  }
+
+ private:
+  bool take_slot(int dev) {
+    Slot* got = nullptr;
+    {
+      std::lock_guard<std::mutex> lk(g_slot_mu);
+      for (Slot& s : g_slots[dev]) {
+        if (s.held || (s.ptr && s.last != stream)) continue;
+        if (s.ptr || !got) got = &s;
+        if (s.ptr) break;
+      }
+      if (!got) return false;
+      got->held = true;
+      got->last = stream;
+    }
+    bool ok;
+    if (got->ptr) {
+      ok = hipStreamWaitEvent(stream, got->done, 0) == hipSuccess;
+    } else {
+      ok = hipEventCreateWithFlags(&got->done, hipEventDisableTiming) == hipSuccess;
+      if (ok && ws_alloc(&got->ptr, kSlotBytes, stream) != hipSuccess) {
+        (void)hipEventDestroy(got->done);
+        got->ptr = nullptr;
+        ok = false;
+      }
+    }
+    if (!ok) {
+      std::lock_guard<std::mutex> lk(g_slot_mu);
+      got->held = false;
+      return false;
+    }
+    slot = got;
+    ptr = got->ptr;
+    return true;
+  }
+};
+
 // diagnostic per-kernel timing (afno_profile_begin / afno_profile_end)
 struct Profile {
   std::mutex mu;
@@ -321,7 +404,9 @@ int run(const Args& a, int stage, float* dst, hipStream_t stream, bool noalloc =
     if (e != hipSuccess) return fail(AFNO_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
     return AFNO_OK;
   }
-  e = ws_alloc(&S, pl.ws_bytes, stream);
+  Workspace ws;
+  e = ws.acquire(pl.ws_bytes, stream);
+  S = ws.ptr;
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(AFNO_ERR_HIP, std::string("workspace allocation of ") +
@@ -329,7 +414,7 @@ int run(const Args& a, int stage, float* dst, hipStream_t stream, bool noalloc =
   }
   hipEvent_t* ev = stage == afno::kStageFull ? profile_slot() : nullptr;
   e = afno::launch_filter(pl, a.x, a.w1, a.b1, a.w2, a.b2, S, a.out, dst, stage, stream, ev);
-  hipError_t ef = hipFreeAsync(S, stream);
+  hipError_t ef = ws.release();
   if (e != hipSuccess) return fail(AFNO_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
   if (ef != hipSuccess) return fail(AFNO_ERR_HIP, std::string("workspace free: ") + hipGetErrorString(ef));
   return AFNO_OK;
@@ -392,16 +477,16 @@ int run_backward(const Args& a, const void* gout, float* dw1, float* db1, float*
   const size_t modes_bytes = (size_t)4 * a.nb * 2 * pl.bs * (size_t)afno::bwd_mpad(pl) * es;
   pl.bwd.acc_offset = pl.bwd.modes_offset + up(modes_bytes);
   pl.bwd.bytes = pl.bwd.acc_offset + afno::bwd_acc_floats(pl) * 4;
-  void* ws = nullptr;
-  e = ws_alloc(&ws, pl.bwd.bytes, stream);
+  Workspace ws;
+  e = ws.acquire(pl.bwd.bytes, stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(AFNO_ERR_HIP, std::string("workspace allocation of ") + std::to_string(pl.bwd.bytes) +
                                   " bytes: " + hipGetErrorString(e));
   }
-  bp.ws = ws;
+  bp.ws = ws.ptr;
   e = afno::launch_backward(pl, bp, stream);
-  hipError_t ef = hipFreeAsync(ws, stream);
+  hipError_t ef = ws.release();
   if (e != hipSuccess) return fail(AFNO_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
   if (ef != hipSuccess) return fail(AFNO_ERR_HIP, std::string("workspace free: ") + hipGetErrorString(ef));
   return AFNO_OK;
@@ -454,16 +539,16 @@ int run_block(const Args& a, const void* ln1_g, const void* ln1_b, const void* l
   bp.wbt_off = bp.wat_off + up(mb);
   bp.s_off = bp.wbt_off + up(mb);
   const size_t bytes = bp.s_off + pl.ws_bytes;
-  void* ws = nullptr;
-  hipError_t e = ws_alloc(&ws, bytes, stream);
+  Workspace ws;
+  hipError_t e = ws.acquire(bytes, stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(AFNO_ERR_HIP, std::string("workspace allocation of ") + std::to_string(bytes) +
                                   " bytes: " + hipGetErrorString(e));
   }
-  bp.ws = static_cast<char*>(ws);
+  bp.ws = static_cast<char*>(ws.ptr);
   e = afno::launch_block(pl, bp, stream);
-  hipError_t ef = hipFreeAsync(ws, stream);
+  hipError_t ef = ws.release();
   if (e != hipSuccess) return fail(AFNO_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
   if (ef != hipSuccess) return fail(AFNO_ERR_HIP, std::string("workspace free: ") + hipGetErrorString(ef));
   return AFNO_OK;
