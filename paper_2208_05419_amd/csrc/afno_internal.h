@@ -42,6 +42,8 @@ struct ColParams {
   int n1, n2;         // H = n1 n2
   int chk;            // channels per chunk of the H transforms
   int chk_inv;        // ceil(2^20 / chk): t / chk = (t chk_inv) >> 20 for t < 1024
+  int overlay;        // bf16: the exchange buffer overlays the tiles (chk = bs)
+  int tw_off;         // the roots, bytes into the LDS
   int threads;
   int wm, wn, mw, nw; // wave grid of the products: wm x wn waves of mw row by nw entry tiles
   int mt;             // row tiles of 16 with a kept row

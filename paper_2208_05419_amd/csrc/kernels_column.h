@@ -8,7 +8,8 @@
 //    exchange, as in kernels_fast.h, chk channels at a time, one task a thread and stage.  The
 //    factors come from small sets, so the lengths are a switch over compile-time DFTs rather
 //    than a kernel per H.  In fp32 the exchange uses the chunk's own columns of the tile; in
-//    bf16, whose tile rows are half as wide, a float buffer [H][chk].
+//    bf16, whose tile rows are half as wide, a float buffer [H][chk], which overlays the tiles
+//    where one chunk takes all channels.
 //  * Block MLP (transposed form): D^T[entry][row] = W^T[entry][k] tile^T[k][row] on the matrix
 //    cores, the weights as fragment words prepared once per call (prep_general_words), so that
 //    a lane ends up with four consecutive entries of one row: one 8- or 16-byte LDS store.
@@ -102,8 +103,8 @@ struct ColMem {
     tile = reinterpret_cast<T*>(m);
     htile = p.htile_bytes ? reinterpret_cast<T*>(m + p.tile_bytes) : tile;
     base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
-    fbuf = base + p.tile_bytes + p.htile_bytes;
-    tw = fbuf + (sizeof(T) == 2 ? p.H * p.chk * 8 : 0);
+    fbuf = p.overlay ? base : base + p.tile_bytes + p.htile_bytes;
+    tw = base + p.tw_off;
   }
   __device__ __forceinline__ float2* roots(void* smem) const {
     return reinterpret_cast<float2*>(reinterpret_cast<char*>(smem) + (tw - base));
@@ -142,7 +143,7 @@ __device__ __forceinline__ void st_pair_at(uint32_t a, float2 z, const bf16*) {
 }
 
 // tile rows h < H = DFT along H of the column at cb (row stride rsb bytes), scaled.  Every
-// thread of the workgroup takes part; ends with a barrier.
+// thread of the workgroup takes part; the caller's barrier ends it.
 template <typename T, int SIZES>
 __device__ __forceinline__ void column_dft(const CBuf<T>& cb, uint32_t rsb, const ColMem<T>& m,
                                            const ColParams& p, float scale) {
@@ -177,7 +178,6 @@ __device__ __forceinline__ void column_dft(const CBuf<T>& cb, uint32_t rsb, cons
                            });
     }
   }
-  __syncthreads();
 }
 
 // the column at cb = inverse DFT along H of the tile's rows, scaled (the tile is used up)
@@ -196,7 +196,7 @@ __device__ __forceinline__ void column_idft(const CBuf<T>& cb, uint32_t rsb, con
       Walk i{m.base + (j * ldt + 2 * (cc + c)) * es, n1 * ldt * es};
       Walk f{fc + c * 8 + j * fs, n1 * fs}, w{m.tw, (uint32_t)j * 8};
       dft_n2<true, SIZES>(n2, j < n1, [&](int) { return ld_pair_at(i.next(), (const T*)nullptr); },
-                          [] { if (!kOwn) __syncthreads(); },  // the chunk's columns have been read
+                          [&] { if (!kOwn || p.overlay) __syncthreads(); },  // the tile has been read
                           [&](int k, float2 v) {
                             float2 r = ld_pair_at(w.next(), kF);
                             r.y = -r.y;
@@ -412,8 +412,8 @@ column_general(T* __restrict__ S, const uint4* __restrict__ wfrag, const T* __re
   const CBuf<T> cb(col, buf_bytes((uint64_t)p.H * rsb));
 
   make_twiddles(mem.roots(smem_raw), p.H);
-  zero_pad_rows(mem.tile, p);
   column_dft<T, SIZES>(cb, rsb, mem, p, p.inv_sqrt_h);
+  __syncthreads();  // (the padding rows H .. H16 - 1 hold anything: no row depends on another)
 
   if (stage != 1) {
     const int wm = wave / p.wn, wn = wave % p.wn;
@@ -584,12 +584,13 @@ column_bwd_general(const T* __restrict__ Sx, T* __restrict__ Sg, const uint4* __
   uint32_t mask[kMaxMW];  // per row tile: bit 4 n + r relu, bit 16 + 4 n + r softshrink
 
   make_twiddles(mem.roots(smem_raw), p.H);
-  zero_pad_rows(tile, p);
 
   // X = F(x) column, then dz = c_kw F(g) column, by the same code
 #pragma unroll 1
   for (int pass = 0; pass < 2; ++pass) {
     column_dft<T, SIZES>(pass ? cg : cx, rsb, mem, p, pass ? p.inv_sqrt_h * ckw : p.inv_sqrt_h);
+    zero_pad_rows(tile, p);  // their factors meet zeros in the weight products' sums
+    __syncthreads();
     if (pass == 0) {
       write_modes<T>(tile, ldt, p.H16, HC, bs, mode_tensor(kModeX), m0);
       // h = relu(X W1 + b1) -> tile, mask v > 0
@@ -637,7 +638,6 @@ column_bwd_general(const T* __restrict__ Sx, T* __restrict__ Sg, const uint4* __
         });
       });
       __syncthreads();  // the h rows are read (products and the h write)
-      zero_pad_rows(tile, p);  // they hold relu(b1)
     }
   }
 
