@@ -466,13 +466,12 @@ int run_backward(const Args& a, const void* gout, float* dw1, float* db1, float*
     if (e != hipSuccess) return fail(AFNO_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
     return AFNO_OK;
   }
-  // workspace: Sx, Sg, conjugate-transposed weights, the matrix-core kernel's prepared
-  // operands, per-mode factors, fp32 product and bias sums
+  // workspace: Sx, Sg, the column kernel's prepared operands, per-mode factors, fp32 product and
+  // bias sums
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   pl.bwd.sx_offset = 0;
   pl.bwd.sg_offset = up(pl.spec_bytes);
-  pl.bwd.wt_offset = pl.bwd.sg_offset + up(pl.spec_bytes);
-  pl.bwd.prep_offset = pl.bwd.wt_offset + (afno::use_mfma_col(pl) ? up(2 * wb) : 0);
+  pl.bwd.prep_offset = pl.bwd.sg_offset + up(pl.spec_bytes);
   pl.bwd.modes_offset = pl.bwd.prep_offset + up(afno::bwd_prep_bytes(pl));
   const size_t modes_bytes = (size_t)4 * a.nb * 2 * pl.bs * (size_t)afno::bwd_mpad(pl) * es;
   pl.bwd.acc_offset = pl.bwd.modes_offset + up(modes_bytes);

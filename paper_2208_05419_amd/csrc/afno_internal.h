@@ -41,7 +41,7 @@ struct ColParams {
   // the size-generic kernels (plan_general_column)
   int n1, n2;         // H = n1 n2
   int chk;            // channels per chunk of the H transforms
-  int chk_inv;        // ceil(2^20 / chk): t / chk = (t chk_inv) >> 20 for t < 1024
+  int chk_inv, bs_inv; // ceil(2^20 / chk): t / chk = (t chk_inv) >> 20 for t < 2^20 / chk; of bs
   int overlay;        // bf16: the exchange buffer overlays the tiles (chk = bs)
   int tw_off;         // the roots, bytes into the LDS
   int threads;
@@ -65,7 +65,7 @@ struct Plan {
   size_t ws_bytes;    // whole workspace
   bool plain_words;   // no room for prepared words: the size-generic kernel gathers the weights
   struct {            // backward-pass workspace offsets (afno_filter_backward)
-    size_t sx_offset, sg_offset, wt_offset, prep_offset, modes_offset, acc_offset, bytes;
+    size_t sx_offset, sg_offset, prep_offset, modes_offset, acc_offset, bytes;
   } bwd;
 };
 

@@ -293,6 +293,7 @@ void plan_general_column(Plan& pl) {
   pl.col_lds = c.overlay ? over : lds(c.chk);
   c.tw_off = (int)(pl.col_lds - (size_t)c.H * 8);
   c.chk_inv = ((1 << 20) + c.chk - 1) / c.chk;
+  c.bs_inv = ((1 << 20) + c.bs - 1) / c.bs;
   c.threads = 64 * std::max(c.wm * c.wn, (c.chk * c.n2 + 63) / 64);
 }
 
@@ -482,16 +483,15 @@ static hipError_t launch_row_forward(const Plan& pl, const T* x, T* S, const Pre
   return hipGetLastError();
 }
 
-static void launch_col_bwd_mfma(const Plan& pl, const bf16* Sx, bf16* Sg, const uint4* wfwd,
-                                const uint4* wbwd, const uint4* tab, const uint4* tab_lo,
-                                const bf16* b1,
+static void launch_col_bwd_mfma(const Plan& pl, const bf16* Sx, bf16* Sg, const uint4* wfrag,
+                                const uint4* tab, const uint4* tab_lo, const bf16* b1,
                                 const bf16* b2, bf16* modes, int64_t mpad, hipStream_t st) {
   const int hp = mfma_col_hp(pl.H);
   const dim3 grid((unsigned)(pl.B * pl.KW * pl.nb));
 #define AFNO_CASE(HP_, BS_)                                                                   \
   if (hp == HP_ && pl.bs == BS_) {                                                            \
     hipLaunchKernelGGL((column_bwd_mfma<HP_, BS_>), grid, dim3(512), (MfmaBwd<HP_, BS_>::kBytes), \
-                       st, Sx, Sg, wfwd, wbwd, tab, tab_lo, b1, b2, (int)pl.H, (int)pl.C, (int)pl.KW,   \
+                       st, Sx, Sg, wfrag, tab, tab_lo, b1, b2, (int)pl.H, (int)pl.C, (int)pl.KW,   \
                        (int)pl.nb, (int)pl.kept_h, pl.col.lam, (int)pl.W, modes, mpad);      \
     return;                                                                                   \
   }
@@ -506,8 +506,6 @@ static hipError_t launch_bwd(const Plan& pl, const BwdPtrs& a, hipStream_t st) {
   char* ws = static_cast<char*>(a.ws);
   T* Sx = reinterpret_cast<T*>(ws + pl.bwd.sx_offset);
   T* Sg = reinterpret_cast<T*>(ws + pl.bwd.sg_offset);
-  T* wt1 = reinterpret_cast<T*>(ws + pl.bwd.wt_offset);
-  T* wt2 = wt1 + pl.nb * pl.bs * pl.bs * 2;
   T* modes = reinterpret_cast<T*>(ws + pl.bwd.modes_offset);
   float* acc = reinterpret_cast<float*>(ws + pl.bwd.acc_offset);
   const int nb = (int)pl.nb, bs = (int)pl.bs, nb2 = 2 * bs;
@@ -530,29 +528,18 @@ static hipError_t launch_bwd(const Plan& pl, const BwdPtrs& a, hipStream_t st) {
   const int64_t nw = (int64_t)2 * nb * bs * bs;
   if constexpr (sizeof(T) == 2) {
     if (mfma) {
-      typedef typename FragWord<T>::type Word;
-      Word* wfwd = reinterpret_cast<Word*>(ws + pl.bwd.prep_offset);
-      Word* wbwd = reinterpret_cast<Word*>(ws + pl.bwd.prep_offset + frag_bytes(pl));
-      uint4* tab = reinterpret_cast<uint4*>(ws + pl.bwd.prep_offset + 2 * frag_bytes(pl));
-      uint4* tab_lo = reinterpret_cast<uint4*>(ws + pl.bwd.prep_offset + 2 * frag_bytes(pl) +
-                                               mfma_tab_bytes(pl));
-      const int hp = mfma_col_hp(pl.H);
-      const int64_t ntab = (int64_t)mfma_tab_bytes(pl) / 16;
-      // the table rounded entry by entry (kept_h -1): tab_lo holds its remainders
-      PrepJob<T> pf{static_cast<const T*>(a.w1), static_cast<const T*>(a.w2), wfwd, tab, nb, bs,
-                    (int)pl.H, hp, 0, -1, 0};
-      PrepJob<T> pb{wt2, wt1, wbwd, nullptr, nb, bs, (int)pl.H, hp, 0, -1, 0};
-      // everything that does not read wt1 / wt2 in one launch, then their fragments
-      BwdPrep bp{pf, static_cast<const bf16*>(a.w1), static_cast<const bf16*>(a.w2), wt1, wt2,
-                 tab_lo, nb, bs, (int)pl.H, hp, prep_words_host(pl, true, -1), ntab, nw};
-      const int64_t nall = bp.n_pf + bp.n_lo + bp.n_ct;
+      uint4* words = reinterpret_cast<uint4*>(ws + pl.bwd.prep_offset);
+      uint4* tab = words + 2 * frag_bytes(pl) / 16;
+      uint4* tab_lo = tab + mfma_tab_bytes(pl) / 16;
+      // the words of all four matrices, the transposed ones straight from the weights, and the
+      // table rounded entry by entry with its remainders (tab_lo): one launch
+      BwdPrep bp{static_cast<const bf16*>(a.w1), static_cast<const bf16*>(a.w2), words, tab, tab_lo,
+                 nb, bs, (int)pl.H, mfma_col_hp(pl.H), (int64_t)general_frag_bytes(pl, 4) / 16,
+                 (int64_t)mfma_tab_bytes(pl) / 16};
+      const int64_t nall = bp.n_words + 2 * bp.n_tab;
       hipLaunchKernelGGL(bwd_prep_kernel, dim3((unsigned)std::min<int64_t>((nall + 255) / 256, 4096)),
                          dim3(256), 0, st, bp);
-      const unsigned gb = (unsigned)std::min<int64_t>((prep_words_host(pl, false, -1) + 255) / 256, 4096);
-      hipLaunchKernelGGL(prep_operands_kernel<T>, dim3(gb), dim3(256), 0, st, pb);
-      launch_col_bwd_mfma(pl, Sx, Sg, reinterpret_cast<const uint4*>(wfwd),
-                          reinterpret_cast<const uint4*>(wbwd), tab, tab_lo,
-                          static_cast<const T*>(a.b1),
+      launch_col_bwd_mfma(pl, Sx, Sg, words, tab, tab_lo, static_cast<const T*>(a.b1),
                           static_cast<const T*>(a.b2), modes, mpad, st);
     }
   }

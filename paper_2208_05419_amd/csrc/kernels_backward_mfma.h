@@ -63,29 +63,26 @@ __device__ __forceinline__ uint4 dft_table_word_lo(int64_t i, int H, int HP) {
   return w.u;
 }
 
-// The backward's independent preparations in one launch, index ranges in turn: the forward
-// operands (block weights in fragment order and the DFT table, PrepJob pf), the table's
-// rounding remainders, and the conjugate-transposed weights.  The fragments of the
-// conjugate-transposed weights read wt1 / wt2 and follow in a launch of their own.
+// The matrix-core backward's prepared operands in one launch, index ranges in turn: the fragment
+// words of W1x, W2x and of their transposes (both gathered from the weights themselves:
+// prep_general_words), the DFT table and the table's rounding remainders.
 struct BwdPrep {
-  PrepJob<bf16> pf;
   const bf16 *w1, *w2;
-  bf16 *wt1, *wt2;
-  uint4* tab_lo;
+  uint4 *words, *tab, *tab_lo;
   int nb, bs, H, HP;
-  int64_t n_pf, n_lo, n_ct;
+  int64_t n_words, n_tab;  // tasks: the words, then n_tab of each table
 };
 
 __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdPrep p) {
-  const int64_t e1 = p.n_pf, e2 = e1 + p.n_lo, e3 = e2 + p.n_ct;
+  const int64_t e1 = p.n_words, e2 = e1 + p.n_tab, e3 = e2 + p.n_tab;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < e3;
        t += (int64_t)gridDim.x * blockDim.x) {
-    if (t < e1)
-      prep_operands<bf16>(t, e3, p.pf, nullptr);  // this word only (the next: t + e3 >= e1)
+    if (t < e1)  // this word only (the next: t + e3 >= e1)
+      prep_general_words<bf16>(t, e3, p.w1, p.w2, p.words, p.nb, p.bs, p.bs, 4);
     else if (t < e2)
-      p.tab_lo[t - e1] = dft_table_word_lo(t - e1, p.H, p.HP);
+      p.tab[t - e1] = dft_table_word(t - e1, p.H, p.HP);
     else
-      conj_transpose_one<bf16>(t - e2, p.w1, p.w2, p.wt1, p.wt2, p.nb, p.bs);
+      p.tab_lo[t - e2] = dft_table_word_lo(t - e2, p.H, p.HP);
   }
 }
 
@@ -275,15 +272,15 @@ __device__ __forceinline__ void bwd_modes_out(const bf16* Rt, bf16* dst, int64_t
 }
 
 // grid B * KW * nb (block index fastest), 512 threads, dynamic LDS MfmaBwd<HP, BS>::kBytes.
-// Sx: spectrum of x; Sg: spectrum of g, replaced by IDFT_H(dX) / c_kw.  wfwd: fragments of
-// (w1, w2); wbwd: fragments of (conj(w2)^T, conj(w1)^T); dtab, dtab_lo: the DFT table and its
+// Sx: spectrum of x; Sg: spectrum of g, replaced by IDFT_H(dX) / c_kw.  wfrag: per
+// block the fragments of W1x, W2x, W2x^T, W1x^T; dtab, dtab_lo: the DFT table and its
 // rounding remainders.  modes: the four
 // per-mode factor tensors (the weight-product pass takes the weight and bias gradients from
 // them).
 template <int HP, int BS>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-column_bwd_mfma(const bf16* __restrict__ Sx, bf16* __restrict__ Sg, const uint4* __restrict__ wfwd,
-                const uint4* __restrict__ wbwd, const uint4* __restrict__ dtab,
+column_bwd_mfma(const bf16* __restrict__ Sx, bf16* __restrict__ Sg, const uint4* __restrict__ wfrag,
+                const uint4* __restrict__ dtab,
                 const uint4* __restrict__ dtab_lo, const bf16* __restrict__ b1, const bf16* __restrict__ b2, int H, int C, int KW,
                 int nb, int kept_h, float lam, int W, bf16* __restrict__ modes, int64_t mpad) {
   typedef MfmaCol<HP, BS> G;
@@ -343,7 +340,7 @@ column_bwd_mfma(const bf16* __restrict__ Sx, bf16* __restrict__ Sg, const uint4*
   {
     const int lane = opq((int)threadIdx.x) & 63, l16 = lane & 15, g = lane >> 4;
     f32x4 acc[G::TMW][G::TNW];
-    bwd_prod_wt<HP, BS>(Buf(wfwd + blk * kBlockWords, (uint32_t)(kBlockWords * 16)), 0, R, lane,
+    bwd_prod_wt<HP, BS>(Buf(wfrag + blk * 2 * kBlockWords, (uint32_t)(kBlockWords * 16)), 0, R, lane,
                         twm, twn, acc);
     float bias[G::TMW][4];
 #pragma unroll
@@ -383,7 +380,7 @@ column_bwd_mfma(const bf16* __restrict__ Sx, bf16* __restrict__ Sg, const uint4*
   {
     const int lane = opq((int)threadIdx.x) & 63, l16 = lane & 15, g = lane >> 4;
     f32x4 acc[G::LMW][G::LNW];
-    bwd_prod_tw<HP, BS>(Buf(wfwd + blk * kBlockWords, (uint32_t)(kBlockWords * 16)), kLayerBytes,
+    bwd_prod_tw<HP, BS>(Buf(wfrag + blk * 2 * kBlockWords, (uint32_t)(kBlockWords * 16)), kLayerBytes,
                         R, lane, lwm, lwn, acc);
     const bool all_rows = kept_h > H / 2;
 #pragma unroll
@@ -437,7 +434,7 @@ column_bwd_mfma(const bf16* __restrict__ Sx, bf16* __restrict__ Sg, const uint4*
   {
     const int lane = opq((int)threadIdx.x) & 63, l16 = lane & 15, g = lane >> 4;
     f32x4 acc[G::TMW][G::TNW];
-    bwd_prod_wt<HP, BS>(Buf(wbwd + blk * kBlockWords, (uint32_t)(kBlockWords * 16)), 0, R, lane,
+    bwd_prod_wt<HP, BS>(Buf(wfrag + (blk * 2 + 1) * kBlockWords, (uint32_t)(kBlockWords * 16)), 0, R, lane,
                         twm, twn, acc);
     __syncthreads();  // DO read by every wave (products, modes)
 #pragma unroll
@@ -461,7 +458,7 @@ column_bwd_mfma(const bf16* __restrict__ Sx, bf16* __restrict__ Sg, const uint4*
   {
     const int lane = opq((int)threadIdx.x) & 63, l16 = lane & 15, g = lane >> 4;
     f32x4 acc[G::LMW][G::LNW];
-    bwd_prod_tw<HP, BS>(Buf(wbwd + blk * kBlockWords, (uint32_t)(kBlockWords * 16)), kLayerBytes,
+    bwd_prod_tw<HP, BS>(Buf(wfrag + (blk * 2 + 1) * kBlockWords, (uint32_t)(kBlockWords * 16)), kLayerBytes,
                         R, lane, lwm, lwn, acc);
     __syncthreads();  // DV read by every wave
 #pragma unroll

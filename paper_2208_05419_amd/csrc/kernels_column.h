@@ -502,44 +502,43 @@ __device__ __forceinline__ void st_stream(T* p, uint4 v) {
 
 // tile rows 0 .. HC - 1 of the block's 2 bs entries -> dst groups m0 / 8 .., 8 rows per task
 // (rows past H16 are zero)
-template <typename T>
-__device__ __forceinline__ void write_modes(const T* tile, int ldt, int H16, int HC, int bs,
-                                            T* dst, int64_t m0) {
-  const int tasks = bs * (HC / 8);
-  const int nb2 = 2 * bs;
+__device__ __forceinline__ void write_modes(const float* tile, const ColParams& p, int HC,
+                                            float* dst, int64_t m0) {
+  const int nb2 = 2 * p.bs, tasks = p.bs * (HC / 8);
   for (int t = opq((int)threadIdx.x); t < tasks; t += blockDim.x) {
-    const int r8 = t / bs, c = t - r8 * bs, r0 = 8 * r8;
-    float re[8], im[8];
+    const int r8 = (int)(((uint32_t)t * (uint32_t)p.bs_inv) >> 20), c = t - r8 * p.bs, r0 = 8 * r8;
+    V16 re[2], im[2];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float2 z = r0 < H16 ? ld_c(tile + (r0 + i) * ldt + 2 * c) : make_float2(0.f, 0.f);
-      re[i] = z.x;
-      im[i] = z.y;
+      const float2 z = r0 < p.H16 ? ld_c(tile + (r0 + i) * p.ldt + 2 * c) : make_float2(0.f, 0.f);
+      re[i / 4].f[i % 4] = z.x;
+      im[i / 4].f[i % 4] = z.y;
     }
-    T* pr = dst + (((m0 + r0) / 8) * nb2 + 2 * c) * 8;
-    T* pi = pr + 8;
-    if constexpr (sizeof(T) == 2) {
-      union { uint4 u; bf16 h[8]; } a, b;
+    float* pr = dst + (((m0 + r0) / 8) * nb2 + 2 * c) * 8;
+    st_stream(pr, re[0].u);
+    st_stream(pr + 4, re[1].u);
+    st_stream(pr + 8, im[0].u);
+    st_stream(pr + 12, im[1].u);
+  }
+}
+__device__ __forceinline__ void write_modes(const bf16* tile, const ColParams& p, int HC, bf16* dst,
+                                            int64_t m0) {
+  const int nb2 = 2 * p.bs, tasks = p.bs * (HC / 8);
+  for (int t = opq((int)threadIdx.x); t < tasks; t += blockDim.x) {
+    const int r8 = (int)(((uint32_t)t * (uint32_t)p.bs_inv) >> 20), c = t - r8 * p.bs, r0 = 8 * r8;
+    uint32_t z[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        a.h[i] = (bf16)re[i];
-        b.h[i] = (bf16)im[i];
-      }
-      st_stream(pr, a.u);
-      st_stream(pi, b.u);
-    } else {
+    for (int i = 0; i < 8; ++i)
+      z[i] = r0 < p.H16 ? *reinterpret_cast<const uint32_t*>(tile + (r0 + i) * p.ldt + 2 * c) : 0u;
+    uint32_t re[4], im[4];  // the low halves and the high halves of two rows each
 #pragma unroll
-      for (int i = 0; i < 8; i += 4) {
-        V16 a, b;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          a.f[e] = re[i + e];
-          b.f[e] = im[i + e];
-        }
-        st_stream(pr + i, a.u);
-        st_stream(pi + i, b.u);
-      }
+    for (int i = 0; i < 4; ++i) {
+      re[i] = __builtin_amdgcn_perm(z[2 * i + 1], z[2 * i], 0x05040100u);
+      im[i] = __builtin_amdgcn_perm(z[2 * i + 1], z[2 * i], 0x07060302u);
     }
+    bf16* pr = dst + (((m0 + r0) / 8) * nb2 + 2 * c) * 8;
+    st_stream(pr, make_uint4(re[0], re[1], re[2], re[3]));
+    st_stream(pr + 8, make_uint4(im[0], im[1], im[2], im[3]));
   }
 }
 
@@ -592,7 +591,7 @@ column_bwd_general(const T* __restrict__ Sx, T* __restrict__ Sg, const uint4* __
     zero_pad_rows(tile, p);  // their factors meet zeros in the weight products' sums
     __syncthreads();
     if (pass == 0) {
-      write_modes<T>(tile, ldt, p.H16, HC, bs, mode_tensor(kModeX), m0);
+      write_modes(tile, p, HC, mode_tensor(kModeX), m0);
       // h = relu(X W1 + b1) -> tile, mask v > 0
       with_grid<WIDE>(p, [&](auto MWc, auto NWc) {
         constexpr int MW = decltype(MWc)::value, NW = decltype(NWc)::value;
@@ -619,7 +618,7 @@ column_bwd_general(const T* __restrict__ Sx, T* __restrict__ Sg, const uint4* __
         }
       });
       __syncthreads();
-      write_modes<T>(tile, ldt, p.H16, HC, bs, mode_tensor(kModeH), m0);
+      write_modes(tile, p, HC, mode_tensor(kModeH), m0);
       // layer 2: only its mask |o| > lam (and the cutoff) is needed
       with_grid<WIDE>(p, [&](auto MWc, auto NWc) {
         constexpr int MW = decltype(MWc)::value, NW = decltype(NWc)::value;
@@ -654,7 +653,7 @@ column_bwd_general(const T* __restrict__ Sx, T* __restrict__ Sg, const uint4* __
   });
   zero_dead_rows(tile, p);
   __syncthreads();
-  write_modes<T>(tile, ldt, p.H16, HC, bs, mode_tensor(kModeDo), m0);
+  write_modes(tile, p, HC, mode_tensor(kModeDo), m0);
 
   // dv = (do W2^H) masked by v > 0, written; then dX = dv W1^H
 #pragma unroll 1
@@ -672,7 +671,7 @@ column_bwd_general(const T* __restrict__ Sx, T* __restrict__ Sg, const uint4* __
       });
     });
     __syncthreads();
-    if (pass == 0) write_modes<T>(tile, ldt, p.H16, HC, bs, mode_tensor(kModeDv), m0);
+    if (pass == 0) write_modes(tile, p, HC, mode_tensor(kModeDv), m0);
   }
   // -> inverse H-DFT -> Sg column / c_kw
   column_idft<T, SIZES>(cg, rsb, mem, p, p.inv_sqrt_h / ckw);
