@@ -626,14 +626,12 @@ hipError_t launch_block(const Plan& pl, const BlockPtrs& a, hipStream_t st) {
   bf16* wat = reinterpret_cast<bf16*>(ws + a.wat_off);
   bf16* wbt = reinterpret_cast<bf16*>(ws + a.wbt_off);
   const bf16* x = static_cast<const bf16*>(a.x);
-  // the MLP weights in the GEMM's [N][K] form
-  hipLaunchKernelGGL(transpose_bf16, dim3((unsigned)((N1 + 31) / 32), (unsigned)((C + 31) / 32)),
-                     dim3(256), 0, st, static_cast<const bf16*>(a.wa), wat, C, N1);
-  hipLaunchKernelGGL(transpose_bf16, dim3((unsigned)((C + 31) / 32), (unsigned)((N1 + 31) / 32)),
-                     dim3(256), 0, st, static_cast<const bf16*>(a.wb), wbt, N1, C);
+  // LN1, and in the launch's first workgroups the MLP weights to the GEMM's [N][K] form
   const unsigned lng = (unsigned)((M + 3) / 4);
-  hipLaunchKernelGGL(layer_norm_kernel, dim3(lng), dim3(256), 0, st, x,
-                     static_cast<const bf16*>(a.ln1_g), static_cast<const bf16*>(a.ln1_b), t, M, C);
+  const int ntile = (C / 64) * (N1 / 64);
+  hipLaunchKernelGGL(layer_norm_kernel, dim3(lng + 2 * (unsigned)ntile), dim3(256), 0, st, x,
+                     static_cast<const bf16*>(a.ln1_g), static_cast<const bf16*>(a.ln1_b), t, M, C,
+                     static_cast<const bf16*>(a.wa), static_cast<const bf16*>(a.wb), wat, wbt, ntile);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = launch_filter(pl, t, a.w1, a.b1, a.w2, a.b2, ws + a.s_off, u, nullptr, kStageFull, st,

@@ -67,6 +67,27 @@ def test_block_deterministic():
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
+@pytest.mark.parametrize("tokens,C", [((1, 1, 2), 128), ((1, 6, 10), 384)],
+                         ids=["2_tokens_C128", "60_tokens_C384"])
+def test_block_mlp_weights_two_byte_aligned(tokens, C):
+    """MLP weights that start on odd 2-byte addresses (the transposes' loads) give the bits of
+    aligned ones; few tokens, so that the launch is mostly weight tiles."""
+    B, H, W = tokens
+    wl = synth.Workload("block", B, H, W, C, 2 if C == 128 else 4, "bf16", 0.01, 1.0)
+    x = to_dev(synth.make_x(wl, seed=2), "bf16")
+    p = {k: to_dev(v, "bf16") for k, v in synth.make_block_params(wl, seed=2, mlp_std=0.05).items()}
+    say(f"[block, odd weight addresses] {B}x{H}x{W}x{C}")
+    ref = afno.block_forward(x, p, wl.num_blocks, 0.01, 1.0)
+    for k in ("wa", "wb"):
+        flat = torch.empty(p[k].numel() + 1, dtype=p[k].dtype, device=p[k].device)
+        flat[1:] = p[k].reshape(-1)
+        p[k] = flat[1:].reshape(p[k].shape)
+        assert p[k].data_ptr() % 4 == 2
+    out = afno.block_forward(x, p, wl.num_blocks, 0.01, 1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
 def test_block_at_the_benchmark_configuration_sampled():
     """The benchmark's block: 90 x 180 x 768, 8 blocks, B = 4, default parameters.  Samples
     are independent through the block (the filter per sample, LayerNorm and the MLP per
