@@ -340,6 +340,14 @@ __device__ __forceinline__ void each_quad(const ColParams& p, int wm, int grp, F
   }
 }
 
+// S(v) with its 'else 0' taken to the letter: a NaN gives 0 too, as it does in the backward
+// kernel's mask |o| > lam, where v - clamp(v, -lam, lam) passes it on.  It costs 0.5 to 1.6 % of a
+// call at 128 x 256 x 512 bf16 (144.6 and 147.2 us against 143.9 and 144.9, on two cards); the
+// clamp with a test for NaN, or copysign(max(|v| - lam, 0), v), 1.0 %.
+__device__ __forceinline__ float shrink_or_zero(float v, float lam) {
+  return fabsf(v) > lam ? v - copysignf(lam, v) : 0.f;
+}
+
 // zeros in the tile's rows outside the live row tiles (cutoff)
 template <typename T>
 __device__ __forceinline__ void zero_dead_rows(T* tile, const ColParams& p) {
@@ -459,7 +467,7 @@ column_general(T* __restrict__ S, const uint4* __restrict__ wfrag, const T* __re
           const bool keep = row_kept(row, p.H, p.kept_h);
           f32x4 v;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] = keep ? softshrink(acc[m][n][r] + bias[n][r], p.lam) : 0.f;
+          for (int r = 0; r < 4; ++r) v[r] = keep ? shrink_or_zero(acc[m][n][r] + bias[n][r], p.lam) : 0.f;
           st_quad(mem.tile + row * ldt + e0, v);
         });
       }

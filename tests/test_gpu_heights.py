@@ -111,3 +111,19 @@ def test_noalloc_without_room_for_prepared_words():
     afno.filter_forward_noalloc(*args, got)
     torch.cuda.synchronize()
     assert torch.equal(want, got)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_softshrink_of_nan_is_zero(dtype):
+    """S(v) = v - lam, v + lam, else 0: a value that is neither above lam nor below -lam gives 0,
+    NaN included (the oracle's definition)."""
+    wl = synth.Workload("nan", 1, 24, 12, 96, 2, dtype, 0.01, 0.7, weight_std=0.1)
+    x_st, w_st = synth.make_x(wl, seed=5), synth.make_weights(wl, seed=5)
+    w_st["b2"] = w_st["b2"].copy()
+    w_st["b2"][1, 7, 0] = np.float32("nan") if dtype == "fp32" else 0x7FC0
+    x, w = to_dev(x_st, dtype), dev_weights(w_st, dtype)
+    out = afno.filter_forward(x, w["w1"], w["b1"], w["w2"], w["b2"], 2, wl.lam, wl.keep)
+    torch.cuda.synchronize()
+    ref, _ = oracle_run(x_st, w_st, wl, stages=True)
+    assert np.isfinite(ref).all()
+    assert max_rel(to_f64(out), ref) <= TOL[dtype]
