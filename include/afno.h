@@ -70,8 +70,9 @@ enum {
  * for fp32, 4 for bf16) stream-ordered on `stream` and frees it stream-ordered, from a
  * memory pool of its own per device that keeps freed memory for later calls (so the
  * largest workspaces in use at once stay allocated until the process ends).  Workspaces up to
- * 32 MB come, outside stream capture, from at most 8 pieces of that pool which the library
- * keeps per device, each ordered behind its last user by an event.
+ * 32 MB come, outside stream capture, from at most 8 pieces of 32 MB of that pool which the
+ * library keeps per device; a stream takes over a piece of another one only when that one's work
+ * in it has ended, and each user is ordered behind the last by an event.
  * The call is asynchronous: it enqueues on `stream` and returns.
  * B == 0 returns AFNO_OK without touching the GPU (x and out may then be NULL).
  * Errors: arguments are validated before any HIP call; on a non-OK return nothing

@@ -13,6 +13,7 @@
 
 #include "afno.h"
 #include "afno_internal.h"
+#include "workspace.h"
 
 namespace {
 
@@ -196,9 +197,8 @@ std::once_flag g_attr_once;
 constexpr size_t kScratchBytes = (size_t)AFNO_NOALLOC_MAX_WORKSPACE;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
-void* g_scratch_ptr[kMaxDevices] = {};
+void* g_scratch_ptr[afno::kMaxDevices] = {};
 
 // The current device's copy of scratch (hipGetSymbolAddress on the first call per device).
 int scratch_address(void** out) {
@@ -208,7 +208,7 @@ int scratch_address(void** out) {
     (void)hipGetLastError();
     return fail(AFNO_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
   }
-  if (dev < 0 || dev >= kMaxDevices)
+  if (dev < 0 || dev >= afno::kMaxDevices)
     return fail(AFNO_ERR_UNSUPPORTED, "device index beyond the library's table of devices");
   std::lock_guard<std::mutex> lk(g_scratch_mu);
   if (!g_scratch_ptr[dev]) {
@@ -223,126 +223,6 @@ int scratch_address(void** out) {
   *out = g_scratch_ptr[dev];
   return AFNO_OK;
 }
-
-// Per-call workspaces come from a stream-ordered memory pool of the library's own, one per
-// device, that keeps freed memory for the next call instead of returning it to the device
-// (release threshold: unbounded), so that a call's allocation and free cost only the pool's
-// bookkeeping (measured: the 90 x 180 x 768 bf16 call takes 2.5 us less than from the
-// device's default pool).  The pool holds the largest workspaces in use at once until the
-// process ends.
-std::mutex g_pool_mu;
-hipMemPool_t g_pool[kMaxDevices] = {};
-
-hipError_t ws_alloc(void** p, size_t bytes, hipStream_t stream) {
-  int dev = -1;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipMallocAsync(p, bytes, stream);
-  hipMemPool_t pool = nullptr;
-  {
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    if (!g_pool[dev]) {
-      hipMemPoolProps props = {};
-      props.allocType = hipMemAllocationTypePinned;
-      props.location.type = hipMemLocationTypeDevice;
-      props.location.id = dev;
-      e = hipMemPoolCreate(&pool, &props);
-      if (e != hipSuccess) return e;
-      uint64_t keep = UINT64_MAX;
-      e = hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-      if (e != hipSuccess) {
-        (void)hipMemPoolDestroy(pool);
-        return e;
-      }
-      g_pool[dev] = pool;
-    }
-    pool = g_pool[dev];
-  }
-  return hipMallocFromPoolAsync(p, bytes, pool, stream);
-}
-
-// Small workspaces (up to kSlotBytes) come from slots of that pool's memory that the library
-// keeps, at most kSlots (256 MB) a device: a pool allocation and free cost the host 16 us a call,
-// more than the three kernels of a small filter take (16 x 32 x 64: 27 us a call from the pool,
-// 15 from a slot, 11 of them the kernels).  A slot belongs to the stream handle that used it last; it is held by one
-// call while that call enqueues, and every later user first makes its stream wait for the event
-// recorded behind the last one, so that a handle which names another stream by then
-// (hipStreamPerThread in another thread, a destroyed and recreated stream) is ordered all the
-// same.  No slot free for the stream, a larger workspace or a stream under capture (whose graph
-// must own its memory): the pool.
-constexpr size_t kSlotBytes = (size_t)32 << 20;
-constexpr int kSlots = 8;
-struct Slot {
-  void* ptr = nullptr;
-  hipEvent_t done = nullptr;
-  hipStream_t last = nullptr;
-  bool held = false;
-};
-std::mutex g_slot_mu;
-Slot g_slots[kMaxDevices][kSlots];
-
-// One call's workspace.
-struct Workspace {
-  void* ptr = nullptr;
-  Slot* slot = nullptr;
-  hipStream_t stream = nullptr;
-
-  hipError_t acquire(size_t bytes, hipStream_t st) {
-    stream = st;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int dev = -1;
-    if (bytes <= kSlotBytes && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices &&
-        hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-        take_slot(dev))
-      return hipSuccess;
-    (void)hipGetLastError();
-    return ws_alloc(&ptr, bytes, st);
-  }
-  // after the call's last launch
-  hipError_t release() {
-    if (!slot) return hipFreeAsync(ptr, stream);
-    hipError_t e = hipEventRecord(slot->done, stream);
-    if (e != hipSuccess) e = hipStreamSynchronize(stream);  // nothing may still use the slot
-    std::lock_guard<std::mutex> lk(g_slot_mu);
-    slot->held = false;
-    return e;
-  }
-
- private:
-  bool take_slot(int dev) {
-    Slot* got = nullptr;
-    {
-      std::lock_guard<std::mutex> lk(g_slot_mu);
-      for (Slot& s : g_slots[dev]) {
-        if (s.held || (s.ptr && s.last != stream)) continue;
-        if (s.ptr || !got) got = &s;
-        if (s.ptr) break;
-      }
-      if (!got) return false;
-      got->held = true;
-      got->last = stream;
-    }
-    bool ok;
-    if (got->ptr) {
-      ok = hipStreamWaitEvent(stream, got->done, 0) == hipSuccess;
-    } else {
-      ok = hipEventCreateWithFlags(&got->done, hipEventDisableTiming) == hipSuccess;
-      if (ok && ws_alloc(&got->ptr, kSlotBytes, stream) != hipSuccess) {
-        (void)hipEventDestroy(got->done);
-        got->ptr = nullptr;
-        ok = false;
-      }
-    }
-    if (!ok) {
-      std::lock_guard<std::mutex> lk(g_slot_mu);
-      got->held = false;
-      return false;
-    }
-    slot = got;
-    ptr = got->ptr;
-    return true;
-  }
-};
 
 // diagnostic per-kernel timing (afno_profile_begin / afno_profile_end)
 struct Profile {
@@ -404,7 +284,7 @@ int run(const Args& a, int stage, float* dst, hipStream_t stream, bool noalloc =
     if (e != hipSuccess) return fail(AFNO_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
     return AFNO_OK;
   }
-  Workspace ws;
+  afno::Workspace ws;
   e = ws.acquire(pl.ws_bytes, stream);
   S = ws.ptr;
   if (e != hipSuccess) {
@@ -476,7 +356,7 @@ int run_backward(const Args& a, const void* gout, float* dw1, float* db1, float*
   const size_t modes_bytes = (size_t)4 * a.nb * 2 * pl.bs * (size_t)afno::bwd_mpad(pl) * es;
   pl.bwd.acc_offset = pl.bwd.modes_offset + up(modes_bytes);
   pl.bwd.bytes = pl.bwd.acc_offset + afno::bwd_acc_floats(pl) * 4;
-  Workspace ws;
+  afno::Workspace ws;
   e = ws.acquire(pl.bwd.bytes, stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -538,7 +418,7 @@ int run_block(const Args& a, const void* ln1_g, const void* ln1_b, const void* l
   bp.wbt_off = bp.wat_off + up(mb);
   bp.s_off = bp.wbt_off + up(mb);
   const size_t bytes = bp.s_off + pl.ws_bytes;
-  Workspace ws;
+  afno::Workspace ws;
   hipError_t e = ws.acquire(bytes, stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();
