@@ -72,7 +72,8 @@ enum {
  * largest workspaces in use at once stay allocated until the process ends).  Workspaces up to
  * 32 MB come, outside stream capture, from at most 8 pieces of 32 MB of that pool which the
  * library keeps per device; a stream takes over a piece of another one only when that one's work
- * in it has ended, and each user is ordered behind the last by an event.
+ * in it has ended, and each user is ordered behind the last by an event.  Pieces no call is
+ * using are given back when a workspace would not fit otherwise.
  * The call is asynchronous: it enqueues on `stream` and returns.
  * B == 0 returns AFNO_OK without touching the GPU (x and out may then be NULL).
  * Errors: arguments are validated before any HIP call; on a non-OK return nothing

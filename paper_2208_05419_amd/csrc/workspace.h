@@ -65,7 +65,8 @@ inline hipError_t ws_alloc(void** p, size_t bytes, hipStream_t stream) {
 //     allocated as calls overlap in time, not one per stream that ever called);
 //  3. one that is not allocated yet;
 //  4. none: the pool, as larger workspaces and streams under capture (whose graph must own its
-//     memory) always do.
+//     memory) always do.  If the device has no memory left for that, the slots that no call holds
+//     are freed and the pool trimmed, once.
 constexpr size_t kSlotBytes = (size_t)32 << 20;
 constexpr int kSlots = 8;
 struct Slot {
@@ -94,6 +95,27 @@ inline bool slot_idle(const Slot& s) {
   return idle;
 }
 
+// The memory of the slots that no call holds, given back to the device (a call whose workspace did
+// not fit): freed behind their last work, in order on `stream`.  True if there was any.
+inline bool free_idle_slots(int dev, hipStream_t stream) {
+  {
+    std::lock_guard<std::mutex> lk(g_slot_mu);
+    bool any = false;
+    for (Slot& s : g_slots[dev]) {
+      if (s.held || !s.ptr || hipStreamWaitEvent(stream, s.done, 0) != hipSuccess ||
+          hipFreeAsync(s.ptr, stream) != hipSuccess)
+        continue;
+      (void)hipEventDestroy(s.done);
+      s.ptr = nullptr;
+      any = true;
+    }
+    if (!any) return false;
+  }
+  if (hipStreamSynchronize(stream) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  return g_pool[dev] && hipMemPoolTrimTo(g_pool[dev], 0) == hipSuccess;
+}
+
 // One call's workspace.
 struct Workspace {
   void* ptr = nullptr;
@@ -109,7 +131,14 @@ struct Workspace {
         take_slot(dev))
       return hipSuccess;
     (void)hipGetLastError();
-    return ws_alloc(&ptr, bytes, st);
+    hipError_t e = ws_alloc(&ptr, bytes, st);
+    if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess && dev >= 0 &&
+        dev < kMaxDevices && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+        cap == hipStreamCaptureStatusNone && free_idle_slots(dev, st)) {
+      (void)hipGetLastError();
+      e = ws_alloc(&ptr, bytes, st);
+    }
+    return e;
   }
   // after the call's last launch
   hipError_t release() {

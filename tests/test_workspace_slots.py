@@ -32,6 +32,7 @@ static std::map<void*, std::vector<Work>> users;  // live allocations: works tha
 static std::set<Work> ended;
 static Work next_work = 1;
 static long live = 0, allocs = 0, synced = 0;
+static long pooled = 0, room = 1 << 20;  // freed pieces the pool keeps; pieces the device has
 static thread_local long thread_id = 0;
 static thread_local hipStreamCaptureMode thread_mode = hipStreamCaptureModeGlobal;
 static bool other_capture = false, fail_record = false;
@@ -47,10 +48,17 @@ hipError_t hipMemPoolCreate(hipMemPool_t* p, const hipMemPoolProps*) { *p = (hip
 hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void*) { return hipSuccess; }
 hipError_t hipMemPoolDestroy(hipMemPool_t) { return hipSuccess; }
 hipError_t hipMallocFromPoolAsync(void** p, size_t, hipMemPool_t, hipStream_t) {
-  LOCK; *p = malloc(1); users[*p]; ++live; ++allocs; return hipSuccess;
+  LOCK;
+  if (live + pooled >= room) return hipErrorOutOfMemory;
+  *p = malloc(1); users[*p]; ++live; ++allocs; return hipSuccess;
 }
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) { LOCK; pooled = 0; return hipSuccess; }
 hipError_t hipMallocAsync(void** p, size_t n, hipStream_t s) { return hipMallocFromPoolAsync(p, n, nullptr, s); }
-hipError_t hipFreeAsync(void* p, hipStream_t) { LOCK; CHECK(users.erase(p) == 1); --live; free(p); return hipSuccess; }
+hipError_t hipFreeAsync(void* p, hipStream_t s) {
+  LOCK;
+  for (Work u : users[p]) CHECK(ended.count(u) || strm(s).before.count(u));
+  CHECK(users.erase(p) == 1); --live; pooled += room < 100; free(p); return hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
   LOCK; *c = strm(s).capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess;
 }
@@ -140,6 +148,20 @@ int main(int, char** argv) {
     CHECK(synced == 1);
     fail_record = false;
     CHECK(call(6));
+  } else if (!strcmp(t, "idle_slots_make_room")) {
+    for (long h = 100; h < 108; ++h) CHECK(call(h));
+    room = live;
+    afno::Workspace held, big;
+    CHECK(held.acquire(10, (hipStream_t)100) == hipSuccess && held.slot);
+    CHECK(big.acquire(afno::kSlotBytes + 1, (hipStream_t)300) == hipSuccess && !big.slot);
+    CHECK(live == 2);  // the held slot and the large workspace
+    launch(held); held.release();
+    launch(big); big.release();
+    streams[{301, 0}].capturing = true;  // a capture can neither free nor wait: the error stays
+    CHECK(call(100));
+    room = live + pooled;
+    afno::Workspace cap;
+    CHECK(cap.acquire(10, (hipStream_t)301) == hipErrorOutOfMemory && live == 1);
   } else if (!strcmp(t, "threads")) {
     std::vector<std::thread> ts;
     for (long k = 1; k <= 8; ++k)
@@ -164,7 +186,8 @@ int main(int, char** argv) {
 
 SCENARIOS = ["streams_that_come_and_go", "overlapping_streams", "one_handle_many_streams",
              "two_calls_at_once_on_one_stream", "captures_and_large_calls_take_the_pool",
-             "queries_leave_a_capture_alone", "a_failed_record_waits", "threads"]
+             "queries_leave_a_capture_alone", "a_failed_record_waits", "idle_slots_make_room",
+             "threads"]
 
 
 @pytest.fixture(scope="module")
