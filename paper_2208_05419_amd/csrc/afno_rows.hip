@@ -110,13 +110,17 @@ void launch_row_inv_fast(const Plan& pl, const T* S, const T* x, T* out, float* 
   template void launch_row_inv_fast<T>(const Plan&, const T*, const T*, T*, float*, int, hipStream_t);
 #if AFNO_ROWS_PART < 0 || AFNO_ROWS_PART == 0
 AFNO_INST_FWD(bf16)
-// a width with a split; offsets within a slice's rows (at most 2 NP / 16 + 1 of them) in 32 bits
+// A width with a split whose byte offsets from a slice's first row stay in 32 bits.  A row alone
+// always does (a grid row and a spectrum column span at most 4 GiB), and a slice stays in one row
+// where C is a multiple of 2 np in both directions.  A slice that runs on covers two rows if C is
+// at least 2 np, at most 2 (W / 2 + 1) C 8 = (W + 2) 8 C bytes of the spectrum, below 2^32 for
+// W C < 2^28; with fewer channels it covers up to four rows of at most 576 x 48 values.
 bool fast_row_available(int64_t W, int64_t C) {
-  bool listed = false;
-#define AFNO_CASE(w) listed = listed || W == w;
+  int np = 0;
+#define AFNO_CASE(w) if (W == w) np = std::max(row_split_fwd(w).np, row_split_inv(w).np);
   AFNO_ROW_WIDTHS(AFNO_CASE)
 #undef AFNO_CASE
-  return listed && W * C < ((int64_t)1 << 27);
+  return np > 0 && (C % (2 * np) == 0 || W * C < ((int64_t)1 << 28));
 }
 #endif
 #if AFNO_ROWS_PART < 0 || AFNO_ROWS_PART == 1

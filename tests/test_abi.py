@@ -358,3 +358,29 @@ def test_noalloc_validates_like_the_forward_and_bounds_its_workspace():
     assert call_noalloc(B=6, **bf) == afno.AFNO_ERR_UNSUPPORTED
     assert "exceeds" in afno.afno_last_error()
     assert call_noalloc(B=50, **bf) == afno.AFNO_ERR_UNSUPPORTED
+
+
+def test_widths_of_the_specialised_row_passes():
+    """afno::fast_row_available(W, C): every even W = 2^a 3^b 5^c from 12 to 576, at any channel
+    count while a slice that runs on into the next row keeps its byte offsets in 32 bits, and at
+    any the entry points take where no slice does (whole multiples of 64 channels)."""
+    import ctypes
+    f = afno.load_library()._ZN4afno18fast_row_availableEll
+    f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int64], ctypes.c_bool
+
+    def smooth(n):
+        for p in (2, 3, 5):
+            while n % p == 0:
+                n //= p
+        return n == 1
+
+    for W in range(1, 1025):
+        assert f(W, 16) == f(W, 768) == (12 <= W <= 576 and W % 2 == 0 and smooth(W)), W
+    for W in (12, 32, 180, 360, 576):
+        top = 2 ** 30 // W // 64 * 64  # the most channels a grid row of 4 GiB of floats holds
+        assert f(W, top)
+        for C in list(range(16, 2 ** 12, 16)) + list(range(2 ** 22 // W, top, top // 97)):
+            C = C // 16 * 16
+            straddles = C % 32 != 0
+            if f(W, C) and straddles and C >= 64:
+                assert 2 * (W // 2 + 1) * C * 8 < 2 ** 32 and 2 * W * C * 4 < 2 ** 32, (W, C)

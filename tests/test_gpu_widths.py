@@ -43,3 +43,24 @@ def test_width(W):
         e_out, e_delta = max_rel(to_f64(out), ref), max_rel(to_f64(delta), st["delta"])
         say(f"  out rel {e_out:.2e}  delta rel {e_delta:.2e}")
         assert np.isfinite(e_out) and e_out <= TOL[dtype] and e_delta <= TOL[dtype]
+
+
+def test_rows_of_many_channels():
+    """A row of more than 2^27 values (W = 360, 393,216 channels), where offsets within a slice's
+    row come near 32 bits: channels at both ends give the bits of a call on them alone."""
+    W, C, bs = 360, 393216, 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+
+    def normal(*shape, std=1.0):
+        return (std * torch.randn(*shape, generator=gen, device="cuda")).to(torch.bfloat16)
+
+    nb = C // bs
+    x = normal(1, 1, W, C)
+    w = [normal(nb, bs, bs, 2, std=0.2), normal(nb, bs, 2, std=0.2), normal(nb, bs, bs, 2, std=0.2),
+         normal(nb, bs, 2, std=0.2)]
+    out = afno.filter_forward(x, *w, nb, 0.01)
+    for lo, hi in ((0, 8), (nb - 8, nb)):
+        part = afno.filter_forward(x[..., lo * bs:hi * bs].contiguous(), *(t[lo:hi].contiguous() for t in w), 8, 0.01)
+        torch.cuda.synchronize()
+        assert torch.equal(out[..., lo * bs:hi * bs], part)
