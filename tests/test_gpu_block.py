@@ -56,6 +56,41 @@ def test_block_parity(case):
     assert e_out <= 2e-2 and e_d <= 2e-2
 
 
+def _mlp_alone(ba, wb):
+    """out of a block whose tokens, filter and norms give 0, so that out = GELU(ba) wb."""
+    C, z = 128, lambda *n: torch.zeros(*n, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    p = {"ln1_g": z(C), "ln1_b": z(C), "w1": z(2, 64, 64, 2), "b1": z(2, 64, 2), "w2": z(2, 64, 64, 2),
+         "b2": z(2, 64, 2), "ln2_g": z(C), "ln2_b": z(C), "wa": z(C, 4 * C), "ba": ba, "wb": wb, "bb": z(C)}
+    out = afno.block_forward(z(1, 1, 2, C), p, 2, 0.01, 1.0)
+    torch.cuda.synchronize()
+    return out
+
+
+def test_block_gelu_over_its_range():
+    """GELU of every hidden unit, read through a wb of unit vectors, against float64 over -16 .. 16:
+    one rounding to bf16 (2^-8 of the value) beside the kernel's 7e-6, and 2e-37 below z = -12.9."""
+    from scipy.special import ndtr
+    for top in (16.0, 3.0):
+        ba = torch.linspace(-top, top, 512, device="cuda").to(torch.bfloat16)
+        ref = to_f64(ba) * ndtr(to_f64(ba))
+        for k in range(4):
+            wb = torch.zeros(512, 128, dtype=torch.bfloat16, device="cuda")
+            wb[128 * k:128 * k + 128] = torch.eye(128, device="cuda").to(torch.bfloat16)
+            r = ref[128 * k:128 * k + 128]
+            err = np.abs(to_f64(_mlp_alone(ba, wb))[0, 0] - r)
+            assert (err <= 2.0 ** -8 * np.abs(r) * 1.01 + 2e-37).all(), (top, k, err.max())
+
+
+@pytest.mark.parametrize("z", [float("inf"), float("-inf"), float("nan")])
+def test_block_gelu_of_infinities_and_nan(z):
+    ba = torch.zeros(512, dtype=torch.bfloat16, device="cuda")
+    ba[5] = z
+    wb = torch.zeros(512, 128, dtype=torch.bfloat16, device="cuda")
+    wb[5] = 1.0
+    got = to_f64(_mlp_alone(ba, wb))
+    assert (got == z).all() if z > 0 else np.isnan(got).all()
+
+
 def test_block_deterministic():
     """No atomics: repeated calls are bitwise equal."""
     wl = synth.Workload("block", 1, 12, 20, 256, 4, "bf16", 0.01, 1.0)
