@@ -61,14 +61,14 @@ size_t hidden_frag_bytes(const Plan& pl);
 
 // tasks of the preparation job: the fragment-ordered weights' words (hidden = true: the
 // hidden-size kernel's), and the DFT table's columns if with_tab
-static int64_t prep_words_host(const Plan& pl, bool with_tab, int kept_h, int kp = 0,
-                               bool hidden = false, int general = 0) {
+static int64_t prep_words_host(const Plan& pl, bool with_tab, int kp = 0, bool hidden = false,
+                               int general = 0) {
   const int hp = mfma_col_hp(pl.H);
   if (general) return (int64_t)general_frag_bytes(pl, general) / 16;
   if (hidden) return (int64_t)hidden_frag_bytes(pl) / 16 + (with_tab ? 2 * hp : 0);
   return pl.nb * (pl.dtype == 0 ? frag_words_per_block<float>((int)pl.bs)
                                 : frag_words_per_block<bf16>((int)pl.bs)) +
-         (with_tab ? (kp > 0 ? kept_table_tasks(hp, kp) : dft_table_tasks(hp, kept_h)) : 0);
+         (with_tab ? (kp > 0 ? kept_table_tasks(hp, kp) : dft_table_tasks(hp)) : 0);
 }
 
 bool fast_col_available(int dtype, int64_t H, int64_t bs) {
@@ -337,7 +337,7 @@ static hipError_t launch_all(const Plan& pl, const void* x, const void* w1, cons
   if (ev && prep_launch) (void)hipEventRecord(ev[0], st);
   if (prep_launch) {
     const unsigned g = (unsigned)std::min<int64_t>(
-        (prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0, pj.general) + 255) / 256, 4096);
+        (prep_words_host(pl, pj.tout != nullptr, pj.kp, pj.hs > 0, pj.general) + 255) / 256, 4096);
     hipLaunchKernelGGL(prep_operands_kernel<T>, dim3(g), dim3(256), 0, st, pj);
   }
   hipError_t e = hipGetLastError();
@@ -345,7 +345,7 @@ static hipError_t launch_all(const Plan& pl, const void* x, const void* w1, cons
   if (ev) (void)hipEventRecord(ev[1], st);
   if (row_fast)
     launch_row_fwd_fast<T>(pl, xt, St, pj,
-                           prep_words_host(pl, pj.tout != nullptr, pj.kept_h, pj.kp, pj.hs > 0, pj.general), st);
+                           prep_words_host(pl, pj.tout != nullptr, pj.kp, pj.hs > 0, pj.general), st);
   else
     hipLaunchKernelGGL(row_r2c_kernel<T>, rgrid, dim3(kRowThreads), pl.row_lds, st, xt, St, pl.row);
   e = hipGetLastError();
@@ -470,7 +470,7 @@ size_t bwd_acc_floats(const Plan& pl) {
 template <typename T>
 static hipError_t launch_row_forward(const Plan& pl, const T* x, T* S, const PrepJob<T>& pj,
                                      hipStream_t st) {
-  const int64_t ntask = prep_words_host(pl, false, -1, 0, false, pj.general);
+  const int64_t ntask = prep_words_host(pl, false, 0, false, pj.general);
   if (pl.path != 1 && fast_row_available(pl.W, pl.C)) {
     launch_row_fwd_fast<T>(pl, x, S, pj, ntask, st);
   } else {
@@ -519,7 +519,7 @@ static hipError_t launch_bwd(const Plan& pl, const BwdPtrs& a, hipStream_t st) {
   const bool mfma = use_mfma_bwd(pl);
   // the size-generic column kernel's words: extra workgroups of the first W-axis launch
   PrepJob<T> pj{static_cast<const T*>(a.w1), static_cast<const T*>(a.w2), nullptr, nullptr, nb, bs,
-                (int)pl.H, 0, 0, -1, 0, bs, 4};
+                (int)pl.H, 0, 0, 0, 0, bs, 4};
   if (!mfma) pj.wout = reinterpret_cast<typename FragWord<T>::type*>(ws + pl.bwd.prep_offset);
   hipError_t e = launch_row_forward<T>(pl, x, Sx, pj, st);
   pj.wout = nullptr;

@@ -74,7 +74,7 @@ template <> struct Mma<bf16> {
     return *reinterpret_cast<const bf16x8*>(row + kbase + 8 * (lane >> 4));
   }
   // B fragment of the real-ified complex weight at output column nu = 2j + sg:
-  //   Wexp[2i + rho][2j + sg] = (Wr, -Wi ; Wi, Wr)[rho][sg]
+  //   Wexp[2i + rho][2j + sg] = (Wr, Wi ; -Wi, Wr)[rho][sg]
   // w points at the block's [n_in][n_out][2] complex weights.  Each dword holds one
   // complex weight (lo = re, hi = im); sg = 0 needs (re, -im), sg = 1 needs (im, re):
   // a byte permutation and a sign flip with per-lane constants, so no lane diverges

@@ -173,7 +173,7 @@ row_r2c_fast(const T* __restrict__ x, T* __restrict__ S, int C, int KW, float sc
   __shared__ float2 F[FN];
   __shared__ float2 tw[W];
   if ((int)blockIdx.x < pj.nprep) {  // the column kernel's operands
-    if (pj.tout && pj.kept_h >= 0) dft_roots(F, pj.H);
+    if (pj.tout) dft_roots(F, pj.H);
     prep_operands<T>((int64_t)blockIdx.x * NT + threadIdx.x, (int64_t)pj.nprep * NT, pj, F);
     return;
   }

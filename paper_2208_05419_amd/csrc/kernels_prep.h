@@ -189,8 +189,8 @@ __device__ __forceinline__ void prep_hidden_words(int64_t i, int64_t stride, con
   }
 }
 
-// One entry of the real-ified complex weight Wx[2 i + rho][2 j + sg] = (Wr, -Wi ; Wi, Wr)[rho][sg]
-// of w [n_in][n_out][2].
+// One entry of the real-ified complex weight Wx[2 i + rho][2 j + sg] = (Wr, Wi ; -Wi, Wr)[rho][sg]
+// of w [n_in][n_out][2]: row vectors (re, im) times it give the complex product.
 template <typename T>
 __device__ __forceinline__ T real_entry(const T* w, int n_out, int row, int col) {
   const T v = w[((int64_t)(row >> 1) * n_out + (col >> 1)) * 2 + ((row ^ col) & 1)];
@@ -229,9 +229,8 @@ __device__ __forceinline__ void prep_general_words(int64_t i, int64_t stride, co
 
 // What to prepare: both layers of every block in fragment order (frag_words_per_block words
 // per block, word ((layer * KSTEPS + s) * NT16 + t) * 64 + lane), then, if tout is set, the
-// DFT table for height H padded to HP: kept_h >= 0, 2 HP column tasks (dft_table_column, the
-// rounding that carries its error over the kept rows; needs dft_roots); kept_h < 0, one task
-// per fragment word (dft_table_word, every entry rounded to nearest).
+// DFT table for height H padded to HP: 2 HP column tasks (dft_table_column, the rounding that
+// carries its error over the kept_h rows; needs dft_roots).
 template <typename T>
 struct PrepJob {
   const T* w1;
@@ -240,28 +239,26 @@ struct PrepJob {
   uint4* tout;
   int nb, bs, H, HP;
   int nprep;   // workgroups the host launch gives the job (placed before its own work)
-  int kept_h;  // the table's rounding, as above
+  int kept_h;  // the table's rounding, as above (unused without a table)
   int kp;      // > 0: the kept-row kernel's two tables for kp kept rows (kept_table_task)
   int hs;      // > 0 and != bs (bf16): the hidden-size kernel's fragments (prep_hidden_words)
   int general; // > 0: the size-generic column kernels' words instead, this many matrices
                // (prep_general_words; hs is set; no table)
 };
 
-__host__ __device__ inline int64_t dft_table_tasks(int HP, int kept_h) {
-  return kept_h >= 0 ? (int64_t)2 * HP : (int64_t)(2 * HP / 32) * (HP / 16) * 64;
-}
+__host__ __device__ inline int64_t dft_table_tasks(int HP) { return (int64_t)2 * HP; }
 
 template <typename T>
 __device__ __forceinline__ int64_t prep_words(const PrepJob<T>& pj) {
   if (sizeof(T) == 2 && pj.hs > 0 && pj.hs != pj.bs)
     return (int64_t)pj.nb * 2 * (2 * pj.bs / 32) * (2 * pj.hs / 16) * 64 + (pj.tout ? 2 * pj.HP : 0);
   return (int64_t)pj.nb * frag_words_per_block<T>(pj.bs) +
-         (pj.tout ? (pj.kp > 0 ? kept_table_tasks(pj.HP, pj.kp) : dft_table_tasks(pj.HP, pj.kept_h))
+         (pj.tout ? (pj.kp > 0 ? kept_table_tasks(pj.HP, pj.kp) : dft_table_tasks(pj.HP))
                   : 0);
 }
 
 // Tasks i, i + stride, ... of the job: one fragment word of the weights each, then the table
-// tasks.  roots: dft_roots' values (needed when pj.tout is set and pj.kept_h >= 0).
+// tasks.  roots: dft_roots' values (needed when pj.tout is set).
 template <typename T>
 __device__ void prep_operands(int64_t i, int64_t stride, const PrepJob<T>& pj,
                               const float2* roots) {
@@ -284,10 +281,8 @@ __device__ void prep_operands(int64_t i, int64_t stride, const PrepJob<T>& pj,
     if (i >= nw) {
       if (pj.kp > 0)
         kept_table_task(i - nw, pj.H, pj.HP, pj.kp, pj.kept_h, roots, pj.tout);
-      else if (pj.kept_h >= 0)
-        dft_table_column((int)(i - nw), pj.H, pj.HP, pj.kept_h, roots, pj.tout);
       else
-        pj.tout[i - nw] = dft_table_word(i - nw, pj.H, pj.HP);
+        dft_table_column((int)(i - nw), pj.H, pj.HP, pj.kept_h, roots, pj.tout);
       continue;
     }
     const int lane = (int)(i & 63);
@@ -308,7 +303,7 @@ __device__ void prep_operands(int64_t i, int64_t stride, const PrepJob<T>& pj,
 template <typename T>
 __global__ void __launch_bounds__(256) prep_operands_kernel(PrepJob<T> pj) {
   __shared__ float2 roots[96];
-  if (pj.tout && pj.kept_h >= 0) dft_roots(roots, pj.H);
+  if (pj.tout) dft_roots(roots, pj.H);
   prep_operands<T>(blockIdx.x * (int64_t)blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x,
                    pj, roots);
 }
