@@ -1,6 +1,8 @@
-// afno_kernels.hip -- launch sequence of the AFNO spectral filter on gfx950: picks the
-// size-specialised kernels of kernels_fast.h where one exists for the grid, else the
-// size-generic kernels of kernels_generic.h.
+// afno_kernels.hip -- launch sequence of the AFNO spectral filter on gfx950.  W-axis passes: those
+// of kernels_fast.h for the widths of afno_rows.hip, else the radix passes of kernels_generic.h.
+// Column pass: on the matrix cores throughout (kernels_mfma.h, kernels_kept_mfma.h,
+// kernels_hidden_mfma.h) or with register transforms (kernels_fast.h) where an instance exists for
+// the height, block and type, else the size-generic kernels of kernels_column.h.
 //
 // Three passes over HBM, all on one spectrum workspace S [B][H][KW][C] (complex,
 // (re, im) interleaved, stored in the filter's dtype; KW = kept_w columns):

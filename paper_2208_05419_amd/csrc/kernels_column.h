@@ -21,13 +21,15 @@
 //
 // Replaces the radix passes over LDS (four or five passes with two barriers each and a copy of
 // every channel chunk on both sides) and weights gathered four bytes at a time from their plain
-// layout.  What bounds it is the vector ALU's issue of the fp32 transforms (338 and 203
-// instructions a thread for the two stages of H = 180), then the latency of the phases between
-// barriers, of two or three columns to a compute unit.  Column pass, before and after: forward
-// 2 x 128 x 256 x 512 bf16 (8 blocks of 64) 302 -> 84 us; backward 72 x 144 x 384 fp32 (8 of
-// 48) 300 -> 101 us, 180 x 360 x 1024 bf16 (32 of 32) 1373 -> 365 us.  The size-specialised
-// kernels of kernels_fast.h, their strides immediate offsets, stay ahead at their few sizes
-// (180 x 32 bf16: 90 us against 141).
+// layout.  Column pass, before and after: forward 2 x 128 x 256 x 512 bf16 (8 blocks of 64) 302 ->
+// 81 us; backward 72 x 144 x 384 fp32 (8 of 48) 300 -> 97 us, 180 x 360 x 1024 bf16 (32 of 32)
+// 1373 -> 339 us.  What bounds it, from counters: in bf16 the vector ALUs' issue of the fp32
+// transforms (forward 56 % of the time busy, 1,806 instructions a wave; backward 63 %, 2,908) and
+// the latency of the phases between barriers (waves wait 52 % of their time, two columns of eight
+// waves to a compute unit; matrix cores 8 and 4 % busy, LDS 17 and 19 %); in the fp32 backward
+// that latency alone (584 columns on 256 compute units, vector ALUs 17 % and matrix cores 25 %
+// busy).  The size-specialised kernels of kernels_fast.h, their strides immediate offsets, stay
+// ahead at their few sizes (180 x 32 bf16: 90 us against 115).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -61,8 +63,12 @@ __device__ __forceinline__ void dft_task(bool act, Ld ld, Mid mid, St st) {
 }
 
 // The second factor's sizes (n2) and the first's (n1); every 5-smooth H <= 192 is n1 n2.  Only
-// H = 162 and 125 need 18 and 25: a kernel with those two beside the others would spill (57
-// registers in fp32), so they have instances of their own.
+// H = 162 and 125 need 18 and 25: a forward kernel with those two beside the others would spill (57
+// registers in fp32), so they have instances of their own.  What spills all the same (registers,
+// and bytes of scratch a lane): the backward in bf16, 4 and 20, with more than eight tiles a wave
+// or H = 162 or 125 15 and 36 (in fp32 8 and 20, the main one none), and the bf16 forward without
+// prepared words 102 and 88.  At 180 x 360 x 1024 in 32 blocks the backward writes 747 MB, 44 more
+// than the factors and the spectrum: its scratch makes up at most that.
 enum { kSizesMain = 0, kSizesBig = 1, kSizesAll = 2 };
 #define AFNO_COL_N2(X) X(1) X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10) X(12) X(15) X(16)
 #define AFNO_COL_N2_BIG(X) X(18) X(25)
@@ -396,10 +402,11 @@ __device__ __forceinline__ void with_grid(const ColParams& p, F f) {
 
 // ------------------------------------------------------------------ forward
 
-// grid B * KW * nb (block index fastest), block p.threads (pl.col_threads), dynamic LDS
-// pl.col_lds.  S updated in place.  stage: 0 full, 1 stop after the forward transform, 2 stop
+// grid B * KW * nb (block index fastest), block p.threads, dynamic LDS pl.col_lds.  S updated in place.  stage: 0 full, 1 stop after the forward transform, 2 stop
 // after the MLP.
-// PLAIN: no prepared words (a workspace without room for them), the weights from w1 and w2.
+// PLAIN: no prepared words (a fixed workspace without room for them), the weights gathered from w1
+// and w2: 1 x 144 x 450 x 1024 bf16 (8 blocks of 128) 618 us a call against 334 with words, and 1,218
+// with the radix passes that this replaced; 1 x 100 x 320 x 1024 fp32 672, 555 and 1,474.
 template <typename T, int SIZES, bool WIDE, bool PLAIN>
 __global__ void __launch_bounds__(1024)
 column_general(T* __restrict__ S, const uint4* __restrict__ wfrag, const T* __restrict__ w1,
