@@ -160,3 +160,28 @@ def test_capture_between_ordinary_calls():
         torch.cuda.synchronize()
         assert torch.equal(out, want) and torch.equal(again, want)
         assert rep > 0 or torch.equal(want, first)
+
+
+def test_streams_created_and_destroyed(calls):
+    """A stream may be destroyed behind its call: the next stream takes the workspace over, or waits
+    for the event where it has the destroyed one's handle."""
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(path)
+    hip.hipStreamCreate.argtypes = [ctypes.POINTER(ctypes.c_void_p)]
+    hip.hipStreamDestroy.argtypes = [ctypes.c_void_p]
+    wl = synth.Workload("slots", 1, 24, 60, 64, 2, "fp32", 0.01, 1.0)
+    w = dev_weights(synth.make_weights(wl, seed=0), "fp32")
+    x = to_dev(synth.make_x(wl, seed=0), "fp32")
+    args = (w["w1"], w["b1"], w["w2"], w["b2"], 2, 0.01)
+    want = afno.filter_forward(x, *args)
+    outs = [torch.full_like(x, float("nan")) for _ in range(24)]
+    torch.cuda.synchronize()
+    n = _slot_calls()
+    for out in outs:
+        h = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(h)) == 0
+        afno.filter_forward(x, *args, out=out, stream=torch.cuda.ExternalStream(h.value))
+        assert hip.hipStreamDestroy(h) == 0
+    _same([(out, want) for out in outs])
+    assert _slot_calls() >= n + 8
