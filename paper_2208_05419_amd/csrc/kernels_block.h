@@ -180,10 +180,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // GELU(z) = z Phi(z).  The lower tail u = Phi(-|z|) = t Q(t) exp(-z^2 / 2), t = 1 / (1 + 0.3 |z|),
 // with Q a degree-7 fit to erfcx(|z| / sqrt 2) / (2 t) on |z| <= 9 (least squares reweighted to a
 // minimax relative error of 5e-8); then z - |z| u above zero and z u below.  Against float64 the
-// result, in single precision, is within 5e-7 of its own size for z > -3, 4e-6 down to -9, 7e-6
-// down to -12.9 (the fit reaches that far), and within 2e-37 below, where the exponential leaves
-// the normal numbers; 0.5 z (1 + erf) has 1e-7 to 2e-7 for |z| < 1, and below loses all digits by
-// z = -6 to the subtraction.  About 25 issue slots a value where erff takes over 60: the epilogue's
+// result, in single precision, is within 7e-7 of its own size for z > -3 and 7e-6 from there to
+// -12.9 (a model in float32 of every step: 4.4e-7 and 6.7e-6; the fit reaches past its 9), and within
+// 2e-37 below, where the exponential leaves the normal numbers; 0.5 z (1 + erf) has 1e-7 to 2e-7
+// for |z| < 1, and below loses all digits by z = -6 to the subtraction.  About 25 issue slots a value where erff takes over 60: the epilogue's
 // values are the exposed part of the first product (64,800 x 3072 x 768: 426 us with erff, 387
 // with this, 320 without any).  |z| is bounded in the tail only (z = +inf gives +inf; -inf and NaN
 // give NaN, as z Phi(z) does).
