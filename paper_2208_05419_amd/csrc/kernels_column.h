@@ -24,8 +24,8 @@
 // layout.  Column pass, before and after: forward 2 x 128 x 256 x 512 bf16 (8 blocks of 64) 302 ->
 // 81 us; backward 72 x 144 x 384 fp32 (8 of 48) 300 -> 97 us, 180 x 360 x 1024 bf16 (32 of 32)
 // 1373 -> 339 us.  What bounds it, from counters: in bf16 the vector ALUs' issue of the fp32
-// transforms (forward 56 % of the time busy, 1,806 instructions a wave; backward 63 %, 2,908) and
-// the latency of the phases between barriers (waves wait 52 % of their time, two columns of eight
+// transforms (forward 54 % of the time busy, 1,758 instructions a wave; backward 63 %, 2,908) and
+// the latency of the phases between barriers (waves wait 53 % of their time, two columns of eight
 // waves to a compute unit; matrix cores 8 and 4 % busy, LDS 17 and 19 %); in the fp32 backward
 // that latency alone (584 columns on 256 compute units, vector ALUs 17 % and matrix cores 25 %
 // busy).  The size-specialised kernels of kernels_fast.h, their strides immediate offsets, stay
